@@ -1261,93 +1261,197 @@ hipError_t launch_workgroup(const uint32_t *params, uint32_t *states, uint32_t s
 //  Hamming-weight dependency: the weight class of a word (popcount <= 14,
 //    15..17, >= 18) and of its successor, counted in a 3x3 table.
 // counts[k * (bins + 9) ..] = gap bins, then the table row-major.
-// Wave w takes the region [w R, (w+1) R) of the stream (R a multiple of 64)
-// and reads it 64 consecutive words per load, SCREEN_LOADS loads per pass,
-// so the pass streams from HBM.  In a 64-word slice the hit lanes form a
-// ballot mask: a hit's previous hit is the highest hit lane below it, else
-// the wave's last hit so far.  Each lane counts the weight pair that ends at
-// its word (its predecessor's class from the lane below, lane 0's from the
-// previous slice's last word) in a register of nine 7-bit fields, added
-// into plain counters every 127 slices, so the counting is vector work.
-// Gaps and pairs across regions are added at the end, in region order.
-constexpr int SCREEN_WAVES = 4;
-constexpr int SCREEN_THREADS = 64 * SCREEN_WAVES;
-constexpr int SCREEN_LOADS = 8;
+// Wave w takes the region [w R, (w+1) R) of the stream (R a multiple of 32)
+// in tiles of 2048 words: 16-byte loads of consecutive words, the next
+// tile's in flight while this one is counted, turned in LDS so that a lane
+// holds 32 consecutive words.  Per word a lane only shifts three bits into
+// registers: class 0 (the sign of popcount - 15), class 2 (the sign of
+// 17 - popcount) and the hit.  All counting is then popcounts of 32-word
+// masks against themselves moved by one word (weight pairs) or by d words
+// (gaps of d - 1); the previous 32 words are the lane below's.  Gaps that
+// SCREEN_D rounds leave open are counted one hit at a time.  Of the weight
+// table only the four corners and the two classes' totals are counted; the
+// class-1 entries follow from the sums.  Gaps across regions are added at
+// the end, in region order.  Bound by its reads: 4000 streams x 2^17 words,
+// one word in four a hit, 363 us, 5.8 TB/s (a hit ballot per 64-word slice
+// and a pair counter per word: 727 us, bound by vector work).
 constexpr uint32_t SCREEN_NONE = 0xFFFFFFFFu;  // no hit yet (positions < count < 2^32)
+constexpr uint32_t SCREEN_TILE = 2048;
+constexpr uint32_t SCREEN_ROW = 36;            // LDS words per lane: 32, padded
 
-__device__ __forceinline__ uint32_t weight_class(uint32_t v) {
-    const uint32_t w = (uint32_t)__builtin_popcount(v);
-    return w <= 14u ? 0u : (w <= 17u ? 1u : 2u);
+// 16-byte loads at any word address (a stream starts at k * count words).
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// Sum over the wave's lanes, for every lane.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += (uint32_t)__shfl_xor((int)v, d, 64);
+    return v;
 }
 
-__global__ void __launch_bounds__(SCREEN_THREADS)
+template <int NW, int D0>
+__global__ void __launch_bounds__(64 * NW)
 screen_kernel(const uint32_t *__restrict__ out, uint64_t count, uint32_t lo, uint32_t hi,
               uint32_t bins, uint64_t *__restrict__ counts) {
+    __shared__ u32x4 turn[NW][64 * SCREEN_ROW / 4];
     __shared__ uint32_t hist[64 + 9];
-    __shared__ uint32_t first_hit[SCREEN_WAVES], last_hit[SCREEN_WAVES];
+    __shared__ uint32_t first_hit[NW], last_hit[NW];
     const uint32_t k = blockIdx.x, tid = threadIdx.x;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63u;
-    for (uint32_t i = tid; i < bins + 9; i += SCREEN_THREADS) hist[i] = 0;
+    for (uint32_t i = tid; i < bins + 9; i += 64 * NW) hist[i] = 0;
     __syncthreads();
     gptr<const uint32_t> x = (gptr<const uint32_t>)(out + (uint64_t)k * count);
-    const uint64_t R = (count + 64 * SCREEN_WAVES - 1) / (64 * SCREEN_WAVES) * 64;
-    const uint64_t r0 = (uint64_t)wave * R < count ? (uint64_t)wave * R : count;
-    const uint64_t r1 = r0 + R < count ? r0 + R : count;
+    const uint32_t n = (uint32_t)count;
+    const uint32_t R = (uint32_t)((count + 32 * NW - 1) / (32 * NW) * 32);
+    const uint32_t r0 = (uint64_t)wave * R < n ? wave * R : n;
+    const uint32_t r1 = n - r0 < R ? n : r0 + R;
     const uint32_t span = hi - lo;  // a hit: v - lo < span
     const uint64_t lanes_below = lane ? ~0ull >> (64u - lane) : 0ull;
-    uint32_t carry = SCREEN_NONE, first = SCREEN_NONE;
-    uint32_t prev_cls = 3u;  // class of the previous full slice's last word; 3 = none
-    uint32_t hw[9] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};  // this lane's pair counts
-    uint64_t packed = 0;     // pair counts of the slices since the last flush, 7 bits each
-    uint32_t since = 0;      // slices since the last flush (uniform)
-    for (uint64_t b0 = r0; b0 < r1; b0 += 64 * SCREEN_LOADS) {
-        uint32_t v[SCREEN_LOADS];
+    uint32_t first = SCREEN_NONE, carry = SCREEN_NONE;  // region's first and last hit so far
+    uint32_t carry_h = 0, carry_z = 0, carry_t = 0;     // masks of the 32 words before the tile
+    if (r0 > 0 && r0 < r1) {  // the word before the region: the first pair's left class
+        const int w = __builtin_popcount(x[r0 - 1]);
+        carry_z = w <= 14 ? 1u : 0u;
+        carry_t = w >= 18 ? 1u : 0u;
+    }
+    uint32_t n00 = 0, n02 = 0, n20 = 0, n22 = 0, c0 = 0, c2 = 0, p0 = 0, p2 = 0;
+    uint32_t gap[D0 > 0 ? D0 : 1];
 #pragma unroll
-        for (int e = 0; e < SCREEN_LOADS; ++e) {
-            const uint64_t j = b0 + 64u * e + lane;
-            v[e] = j < r1 ? x[j] : 0u;
+    for (int d = 0; d < D0; ++d) gap[d] = 0;
+    u32x4 v[8];
+    auto load = [&](uint32_t b) {  // words b + 256 q + 4 lane ..., zeros past the region
+        if (r1 - b >= SCREEN_TILE) {
+            gptr<const u32x4u> p = (gptr<const u32x4u>)(x + b + 4 * lane);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = p[64 * q];
+        } else {
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t j = b + 256u * q + 4u * lane + e;
+                    v[q][e] = j < r1 ? x[j] : 0u;
+                }
         }
+    };
+    if (r0 < r1) load(r0);
+    for (uint32_t b = r0; b < r1;) {
+        u32x4 *row = turn[wave];
 #pragma unroll
-        for (int e = 0; e < SCREEN_LOADS; ++e) {
-            const uint64_t base = b0 + 64u * e;
-            if (base >= r1) break;  // uniform
-            const uint64_t j = base + lane;
-            const bool valid = j < r1;
-            const bool hit = valid && v[e] - lo < span;
-            const uint64_t m = __builtin_amdgcn_ballot_w64(hit);
-            if (hit) {
-                const uint64_t bm = m & lanes_below;
-                const uint32_t prev = bm ? (uint32_t)base + 63u - (uint32_t)__builtin_clzll(bm)
-                                         : carry;
-                if (prev != SCREEN_NONE) {
-                    const uint32_t gap = (uint32_t)j - prev - 1u;
-                    atomicAdd(&hist[gap < bins - 1u ? gap : bins - 1u], 1u);
+        for (int q = 0; q < 8; ++q)
+            row[(8 * q + (lane >> 3)) * (SCREEN_ROW / 4) + (lane & 7u)] = v[q];
+        group_sync<64>();
+        u32x4 t[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) t[q] = row[lane * (SCREEN_ROW / 4) + q];
+        group_sync<64>();
+        const uint32_t mine = b + 32u * lane;  // this lane's first word
+        const uint32_t left = r1 - b > 32u * lane ? r1 - b - 32u * lane : 0u;
+        b = r1 - b > SCREEN_TILE ? b + SCREEN_TILE : r1;
+        if (b < r1) load(b);
+        uint32_t Z = 0, T = 0, H = 0;  // first word in bit 31
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t w = t[q][e];
+                const uint32_t low = (uint32_t)__builtin_popcount(w) - 15u;
+                Z = __builtin_amdgcn_alignbit(Z, low, 31);
+                T = __builtin_amdgcn_alignbit(T, 2u - low, 31);
+                H = H + H + (w - lo < span ? 1u : 0u);
+            }
+        const uint32_t valid = left >= 32u ? ~0u : ~(~0u >> left);
+        Z &= valid;
+        T &= valid;
+        H &= valid;
+        uint32_t zp = (uint32_t)__shfl_up((int)Z, 1, 64), tp = (uint32_t)__shfl_up((int)T, 1, 64),
+                 hp = (uint32_t)__shfl_up((int)H, 1, 64);
+        if (lane == 0) {
+            zp = carry_z;
+            tp = carry_t;
+            hp = carry_h;
+        }
+        carry_z = (uint32_t)__builtin_amdgcn_readlane((int)Z, 63);
+        carry_t = (uint32_t)__builtin_amdgcn_readlane((int)T, 63);
+        carry_h = (uint32_t)__builtin_amdgcn_readlane((int)H, 63);
+        // left classes of the pairs that end at this lane's words
+        const uint32_t zl = __builtin_amdgcn_alignbit(zp, Z, 1) & valid;
+        const uint32_t tl = __builtin_amdgcn_alignbit(tp, T, 1) & valid;
+        n00 += (uint32_t)__builtin_popcount(zl & Z);
+        n02 += (uint32_t)__builtin_popcount(zl & T);
+        n20 += (uint32_t)__builtin_popcount(tl & Z);
+        n22 += (uint32_t)__builtin_popcount(tl & T);
+        c0 += (uint32_t)__builtin_popcount(Z);
+        c2 += (uint32_t)__builtin_popcount(T);
+        p0 += (uint32_t)__builtin_popcount(zl);
+        p2 += (uint32_t)__builtin_popcount(tl);
+        // hits whose previous hit lies d words before them, d = 1 .. D0
+        uint32_t open = H;
+#pragma unroll
+        for (int d = 1; d <= D0; ++d) {
+            const uint32_t hd = __builtin_amdgcn_alignbit(hp, H, d);
+            gap[d - 1] += (uint32_t)__builtin_popcount(open & hd);
+            open &= ~hd;
+        }
+        const uint64_t any = __builtin_amdgcn_ballot_w64(H != 0u);
+        if (any) {
+            const uint32_t last = mine + 31u - (uint32_t)__builtin_ctz(H | 0x80000000u);
+            if (__builtin_amdgcn_ballot_w64(open != 0u)) {
+                // the last hit before this lane's words
+                const uint64_t below = any & lanes_below;
+                const uint32_t from =
+                    (uint32_t)__shfl((int)last, below ? 63 - __builtin_clzll(below) : 0, 64);
+                const uint32_t before = below ? from : carry;
+                while (open) {
+                    const uint32_t i = (uint32_t)__builtin_clz(open);  // word mine + i
+                    open &= ~(0x80000000u >> i);
+                    const uint32_t earlier = i ? H >> (32u - i) : 0u;
+                    const uint32_t prev =
+                        earlier ? mine + i - 1u - (uint32_t)__builtin_ctz(earlier) : before;
+                    if (prev != SCREEN_NONE) {
+                        const uint32_t g = mine + i - prev - 1u;
+                        atomicAdd(&hist[g < bins - 1u ? g : bins - 1u], 1u);
+                    }
                 }
             }
-            if (m) {
-                if (first == SCREEN_NONE) first = (uint32_t)base + (uint32_t)__builtin_ctzll(m);
-                carry = (uint32_t)base + 63u - (uint32_t)__builtin_clzll(m);
+            if (first == SCREEN_NONE) {
+                const int at = __builtin_ctzll(any);
+                first = (uint32_t)__builtin_amdgcn_readlane(
+                    (int)(mine + (uint32_t)__builtin_clz(H | 1u)), at);
             }
-            // the pair (j-1, j): j-1's class from the lane below, lane 0's
-            // from the previous slice (3 at the region's start: no pair)
-            const uint32_t c = weight_class(v[e]);
-            const uint32_t below_c = (uint32_t)__shfl_up((int)c, 1, 64);
-            const uint32_t pc = lane ? below_c : prev_cls;
-            if (valid && pc < 3u) packed += 1ull << (7u * (3u * pc + c));
-            // a full slice's last word precedes the next slice's first
-            prev_cls = base + 64u <= r1 ? (uint32_t)__shfl((int)c, 63, 64) : 3u;
-            if (++since == 127u) {
-#pragma unroll
-                for (int q = 0; q < 9; ++q) hw[q] += (uint32_t)(packed >> (7 * q)) & 127u;
-                packed = 0;
-                since = 0;
-            }
+            carry = (uint32_t)__builtin_amdgcn_readlane((int)last, 63 - __builtin_clzll(any));
         }
     }
+    if (r0 < r1) {
 #pragma unroll
-    for (int q = 0; q < 9; ++q) {
-        hw[q] += (uint32_t)(packed >> (7 * q)) & 127u;
-        if (hw[q]) atomicAdd(&hist[bins + q], hw[q]);
+        for (int d = 0; d < D0; ++d) {
+            const uint32_t g = wave_sum(gap[d]);
+            if (lane == 0 && g)
+                atomicAdd(&hist[(uint32_t)d < bins - 1u ? (uint32_t)d : bins - 1u], g);
+        }
+        n00 = wave_sum(n00);
+        n02 = wave_sum(n02);
+        n20 = wave_sum(n20);
+        n22 = wave_sum(n22);
+        c0 = wave_sum(c0);
+        c2 = wave_sum(c2);
+        p0 = wave_sum(p0);
+        p2 = wave_sum(p2);
+        uint32_t pairs = r1 - r0;
+        if (r0 == 0) {  // the stream's first word ends no pair
+            const int w = __builtin_popcount(x[0]);
+            --pairs;
+            c0 -= w <= 14 ? 1u : 0u;
+            c2 -= w >= 18 ? 1u : 0u;
+        }
+        if (lane == 0) {
+            const uint32_t n01 = p0 - n00 - n02, n21 = p2 - n20 - n22;
+            const uint32_t n10 = c0 - n00 - n20, n12 = c2 - n02 - n22;
+            const uint32_t tab[9] = {n00, n01, n02, n10, pairs - p0 - p2 - n10 - n12, n12,
+                                     n20, n21, n22};
+#pragma unroll
+            for (int q = 0; q < 9; ++q) atomicAdd(&hist[bins + q], tab[q]);
+        }
     }
     if (lane == 0) {
         first_hit[wave] = first;
@@ -1357,30 +1461,52 @@ screen_kernel(const uint32_t *__restrict__ out, uint64_t count, uint32_t lo, uin
     if (tid == 0) {
         // gaps across regions, in region order
         uint32_t pl = SCREEN_NONE;
-        for (int w = 0; w < SCREEN_WAVES; ++w) {
+        for (int w = 0; w < NW; ++w) {
             if (first_hit[w] == SCREEN_NONE) continue;
             if (pl != SCREEN_NONE) {
-                const uint32_t gap = first_hit[w] - pl - 1u;
-                hist[gap < bins - 1u ? gap : bins - 1u] += 1u;
+                const uint32_t g = first_hit[w] - pl - 1u;
+                hist[g < bins - 1u ? g : bins - 1u] += 1u;
             }
             pl = last_hit[w];
         }
-        // weight pairs across regions
-        for (int w = 0; w + 1 < SCREEN_WAVES; ++w) {
-            const uint64_t e = (uint64_t)(w + 1) * R;
-            if (e < count) hist[bins + 3u * weight_class(x[e - 1]) + weight_class(x[e])] += 1u;
-        }
     }
     __syncthreads();
-    for (uint32_t i = tid; i < bins + 9; i += SCREEN_THREADS)
+    for (uint32_t i = tid; i < bins + 9; i += 64 * NW)
         counts[(uint64_t)k * (bins + 9) + i] = hist[i];
+}
+
+template <int NW>
+static void launch_screen_n(const uint32_t *out, uint32_t n_streams, uint64_t count, uint32_t lo,
+                            uint32_t hi, uint32_t bins, uint64_t *counts, hipStream_t s) {
+    // Rounds of whole-mask gap counting (four operations per 32 words each)
+    // against one loop turn per hit left open in the busiest lane: words
+    // hit more often than 1 in 12 leave few hits after 16 rounds (1 in 2:
+    // after 8), rarer hits are counted one at a time from the start.
+    const uint32_t span = hi - lo;
+    const dim3 grid(n_streams), block(64 * NW);
+    if (span >= (1u << 30) + (1u << 29))
+        hipLaunchKernelGGL((screen_kernel<NW, 8>), grid, block, 0, s, out, count, lo, hi, bins,
+                           counts);
+    else if (span >= (1u << 28) + (1u << 26))
+        hipLaunchKernelGGL((screen_kernel<NW, 16>), grid, block, 0, s, out, count, lo, hi, bins,
+                           counts);
+    else
+        hipLaunchKernelGGL((screen_kernel<NW, 0>), grid, block, 0, s, out, count, lo, hi, bins,
+                           counts);
 }
 
 hipError_t launch_screen(const uint32_t *out, uint32_t n_streams, uint64_t count, uint32_t lo,
                          uint32_t hi, uint32_t bins, uint64_t *counts, hipStream_t s) {
     (void)hipGetLastError();  // report this launch only
-    hipLaunchKernelGGL(screen_kernel, dim3(n_streams), dim3(SCREEN_THREADS), 0, s, out, count,
-                       lo, hi, bins, counts);
+    // Waves per stream: one where a stream is at most two tiles, 16 where
+    // fewer than two workgroups per CU would run (streams are not shared
+    // between workgroups), else four.
+    if (count <= 2 * SCREEN_TILE)
+        launch_screen_n<1>(out, n_streams, count, lo, hi, bins, counts, s);
+    else if (n_streams < 512 && count > 16 * SCREEN_TILE)
+        launch_screen_n<16>(out, n_streams, count, lo, hi, bins, counts, s);
+    else
+        launch_screen_n<4>(out, n_streams, count, lo, hi, bins, counts, s);
     return hipGetLastError();
 }
 
