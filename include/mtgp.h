@@ -259,7 +259,7 @@ typedef struct mtgp_tuning {
                                least number of dependent steps per segment:
                                a batch splits the streams that need more
                                steps than max(this, a multiple (0.75 to
-                               1.25) of its total steps over the streams
+                               1) of its total steps over the streams
                                the device runs at once) */
     int window_below_w;     /* with threads_per_stream = 64, streams with a
                                linear rec_tbl and step width W = N - pos below

@@ -11,7 +11,7 @@
 //   A: a prefix item: the first P = D+1 outputs, also dumping x_0..x_{N+D};
 //   B: one jump per later segment, which starts at output c*lseg
 //      (c >= c0 = ceil((P+1)/lseg)): its state from g_c = x^(c*lseg-1) mod p,
-//      evaluated as one item per 512 state words;
+//      evaluated in passes of jump_words(N) state words;
 //   C: every segment (the first one continues after the prefix up to
 //      c0*lseg), each checking its end state against the next segment's
 //      start state.
@@ -205,6 +205,8 @@ static int ensure_jumps(const std::shared_ptr<ParamSet> &ps, const void *d_param
     const int V = mexp + 64;                 // verification outputs per stream
     const int PW = (mexp + 2 + 31) / 32 + 1; // packed words of p
     const int chunk = 512;
+    const int vwords = jump_words(N);                      // words of a check block
+    const int vpasses = (mexp + vwords - 1) / vwords;      // blocks of a stream's check
     hipError_t e;
     DevBuf d_seeded;
     if (std::find(from_seed.begin(), from_seed.end(), 1) != from_seed.end()) {
@@ -220,7 +222,7 @@ static int ensure_jumps(const std::shared_ptr<ParamSet> &ps, const void *d_param
         (e = d_out.alloc((size_t)cn * (R - N) * 4)) != hipSuccess ||
         (e = d_items.alloc((size_t)cn * sizeof(BatchItem))) != hipSuccess ||
         (e = d_counter.alloc(256)) != hipSuccess ||
-        (e = d_jitems.alloc((size_t)cn * JUMP_BLOCK * sizeof(JumpItem))) != hipSuccess ||
+        (e = d_jitems.alloc((size_t)cn * vpasses * sizeof(JumpBlock))) != hipSuccess ||
         (e = d_poly.alloc((size_t)cn * PW * 4)) != hipSuccess ||
         (e = d_vout.alloc((size_t)cn * V * 4)) != hipSuccess)
         return hip_fail(e, "hipMalloc(jump planning)");
@@ -274,9 +276,7 @@ static int ensure_jumps(const std::shared_ptr<ParamSet> &ps, const void *d_param
                 P[j] = annihilator(&raw[(size_t)j * R], R, pass == 0 ? quick : all);
             });
             // device check: y_t = sum_i p_i x_{t+i} must vanish for t = 1..D
-            // one item per block: each stream's check runs on its own
-            std::vector<JumpItem> jit((size_t)m * JUMP_BLOCK);
-            std::memset(jit.data(), 0, jit.size() * sizeof(JumpItem));
+            std::vector<JumpBlock> jit;
             std::vector<uint32_t> pw((size_t)m * PW, 0u);
             int nj = 0;
             std::vector<int> which;
@@ -286,25 +286,30 @@ static int ensure_jumps(const std::shared_ptr<ParamSet> &ps, const void *d_param
                 if (D < 1 || D > mexp) continue;
                 const std::vector<uint32_t> w = pack32(P[j], D + 1);
                 std::memcpy(&pw[(size_t)nj * PW], w.data(), w.size() * 4);
-                JumpItem &ji = jit[(size_t)nj * JUMP_BLOCK];
-                ji.raw = (uint64_t)(uintptr_t)((uint32_t *)d_raw.p + (size_t)j * R);
-                ji.poly = (uint64_t)(uintptr_t)((uint32_t *)d_poly.p + (size_t)nj * PW);
-                ji.out = (uint64_t)(uintptr_t)((uint32_t *)d_vout.p + (size_t)nj * V);
-                ji.nbits = (uint32_t)(D + 1);
-                ji.m = (uint32_t)mexp;
+                for (int v0 = 0; v0 < mexp; v0 += vwords) {
+                    JumpBlock jb;
+                    jb.raw = (uint64_t)(uintptr_t)((uint32_t *)d_raw.p + (size_t)j * R + v0);
+                    jb.poly = (uint64_t)(uintptr_t)((uint32_t *)d_poly.p + (size_t)nj * PW);
+                    jb.out = (uint64_t)(uintptr_t)((uint32_t *)d_vout.p + (size_t)nj * V + v0);
+                    jb.poly_stride = (uint32_t)w.size();
+                    jb.out_stride = 0;
+                    jb.nbits = (uint32_t)(D + 1);
+                    jb.m = (uint32_t)std::min(vwords, mexp - v0);
+                    jb.n_jumps = 1;
+                    jb.dep = 0;
+                    jit.push_back(jb);
+                }
                 which.push_back(j);
                 ++nj;
             }
             if (nj == 0) break;
             if ((e = hipMemcpyAsync(d_poly.p, pw.data(), (size_t)nj * PW * 4,
                                     hipMemcpyHostToDevice, s)) != hipSuccess ||
-                (e = hipMemcpyAsync(d_jitems.p, jit.data(),
-                                    (size_t)nj * JUMP_BLOCK * sizeof(JumpItem),
+                (e = hipMemcpyAsync(d_jitems.p, jit.data(), jit.size() * sizeof(JumpBlock),
                                     hipMemcpyHostToDevice, s)) != hipSuccess)
                 return hip_fail(e, "hipMemcpyAsync(check items)");
-            if ((e = launch_jump((const JumpItem *)d_jitems.p, (uint32_t)nj * JUMP_BLOCK,
-                                 device_cus(), s)) !=
-                hipSuccess)
+            if ((e = launch_jump(N, (const JumpBlock *)d_jitems.p, (uint32_t)jit.size(),
+                                 device_cus(), s)) != hipSuccess)
                 return hip_fail(e, "jump kernel (check)");
             if ((e = hipMemcpyAsync(vout.data(), d_vout.p, (size_t)nj * V * 4,
                                     hipMemcpyDeviceToHost, s)) != hipSuccess ||
@@ -400,7 +405,7 @@ struct Seg {
 };
 
 struct Layout {
-    size_t off_A = 0, off_B = 0, off_C = 0, off_F = 0, off_rec = 0, off_jdep = 0, off_pflag = 0;
+    size_t off_A = 0, off_B = 0, off_C = 0, off_F = 0, off_rec = 0, off_pflag = 0;
     size_t off_poly = 0, up_end = 0;
     size_t off_raw = 0, off_js = 0, total = 0;
 };
@@ -432,10 +437,11 @@ static uint64_t effective_target(const ParamSet &ps, const std::vector<Request> 
     const uint64_t slots = (uint64_t)std::max(1, per_cu) * (uint64_t)std::max(1, device_cus());
     // a multiple of the balanced share of steps per resident stream: more,
     // shorter segments shorten the tail of the segment phase but every
-    // segment costs a jump (D N / 4 word operations); measured optimum about
-    // 0.75 at mexp 11213 and 1.25 at 23209 and 44497 (jumps 4-16x dearer)
+    // segment costs a jump; measured optimum 0.75 at mexp 11213 (128 x 2^24:
+    // 2.78 ms, 2.80 at 0.5, 2.86 at 1) and 1 at 23209, where jumps are 4x
+    // dearer (4096 x 2^20: 5.24 ms, 5.27 at 0.75, 5.32 at 1.25)
     const uint64_t share = total / slots;
-    const uint64_t adaptive = ps.N <= 400 ? share * 3 / 4 : share * 5 / 4;
+    const uint64_t adaptive = ps.N <= 400 ? share * 3 / 4 : share;
     return std::max<uint64_t>((uint64_t)t.jump_target_steps, adaptive);
 }
 
@@ -476,9 +482,22 @@ static bool wants_split(const ParamSet &ps, const Request &r, uint64_t T, const 
     return (r.count + so - 1) / so > T && r.count > (uint64_t)ps.mexp + 128;
 }
 
-// Jump items per jump: one per JUMP_OUT_WORDS words of the N-word state.
-static size_t jump_passes(int N) {
-    return ((size_t)N + JUMP_OUT_WORDS - 1) / JUMP_OUT_WORDS;
+constexpr int JUMP_BLOCKS_PER_CU = 3;
+
+// Jumps per block: eight where that leaves the CUs three blocks each (the
+// planes of a block product are then built for eight jumps), else four or
+// two (two or four half-waves share a jump), so that a batch with few jumps
+// still reaches every CU.  Prefix-and-jump launch of 100 mexp-11213 streams
+// of 10^6 outputs 190 us (249 with eight always), of 128 x 2^24 520 us (774
+// with four from twelve blocks a CU on).
+static int jumps_per_block(const ParamSet &ps, const std::vector<Seg> &segs) {
+    size_t jumps = 0;
+    for (const Seg &g : segs) jumps += (size_t)(g.C > 1 ? g.C - 1 : 0);
+    jumps *= (size_t)jump_passes(ps.N);
+    const size_t want = (size_t)std::max(1, device_cus()) * JUMP_BLOCKS_PER_CU;
+    int per = JUMP_BLOCK;
+    while (per > 2 && jumps < want * (size_t)per) per /= 2;
+    return per;
 }
 
 static Layout layout_for(const ParamSet &ps, const std::vector<Seg> &segs) {
@@ -489,7 +508,7 @@ static Layout layout_for(const ParamSet &ps, const std::vector<Seg> &segs) {
             continue;
         }
         ++nA;
-        nB += ((size_t)g.C - 1 + JUMP_BLOCK - 1) / JUMP_BLOCK * JUMP_BLOCK * jump_passes(ps.N);
+        nB += ((size_t)g.C - 1 + 1) / 2 * (size_t)jump_passes(ps.N);  // at least two a block
         nC += (size_t)g.C;
         poly_words += ((size_t)g.C - 1) * (((size_t)g.Dsize + 31) / 32);
         raw_words += ((size_t)ps.N + (size_t)g.Dsize + 1 + 63) / 64 * 64;
@@ -498,11 +517,10 @@ static Layout layout_for(const ParamSet &ps, const std::vector<Seg> &segs) {
     Layout L;
     L.off_A = HDR_BYTES;
     L.off_B = L.off_A + al256(nA * sizeof(BatchItem));
-    L.off_C = L.off_B + al256(nB * sizeof(JumpItem));
+    L.off_C = L.off_B + al256(nB * sizeof(JumpBlock));
     L.off_F = L.off_C + al256(nC * sizeof(BatchItem));
     L.off_rec = L.off_F + al256(nA * sizeof(BatchItem));
-    L.off_jdep = L.off_rec + al256(nA * sizeof(ReqRec));
-    L.off_pflag = L.off_jdep + al256(nB / JUMP_BLOCK * 4);
+    L.off_pflag = L.off_rec + al256(nA * sizeof(ReqRec));
     L.off_poly = L.off_pflag + al256(nA * 4);
     L.up_end = L.off_poly + al256(poly_words * 4);
     L.off_raw = L.up_end;
@@ -679,8 +697,7 @@ static int launch_phases(const ParamSet &ps, const void *d_params, char *ws, con
     };
     if (w.nA || w.nB) {  // prefix items and jump blocks, one launch
         if ((e = launch_prefix_jumps(ps.N, (const BatchItem *)(ws + w.off_A), w.nA,
-                                     (const JumpItem *)(ws + w.off_B), w.nB,
-                                     (const uint32_t *)(ws + w.off_jdep),
+                                     (const JumpBlock *)(ws + w.off_B), w.nB,
                                      (uint32_t *)(ws + w.off_pflag), (const uint32_t *)d_params,
                                      hdr, (uint32_t)t.window_below_w, device_cus(), s)) !=
             hipSuccess)
@@ -782,10 +799,11 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
     };
     std::vector<CItem> C;
     std::vector<std::tuple<uint64_t, BatchItem, size_t>> A;  // steps, item, split index
-    std::vector<std::vector<JumpItem>> Bs;                   // per split request, padded
+    std::vector<std::vector<JumpBlock>> Bs;                  // per split request
     std::vector<BatchItem> F;
     std::vector<int32_t> split_streams;
     size_t raw_off = L.off_raw, js_off = L.off_js, poly_off = L.off_poly;
+    const int per_block = jumps_per_block(*ps, segs);
     for (size_t i = 0; i < reqs.size(); ++i) {
         const Request &r = reqs[i];
         const Seg &g = segs[i];
@@ -840,33 +858,30 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
         A.emplace_back((P + so - 1) / so, a, ri);
         // B: jumps, segment k >= 1 starts at output (c0+k-1)*lseg and
         // its state is x^((c0+k-1)*lseg - 1) mod p applied to the words;
-        // each jump is evaluated in passes of JUMP_OUT_WORDS state words
-        // (blocks of JUMP_BLOCK jumps per pass), word m0 onwards reading the
-        // raw words from m0 on
+        // up to per_block jumps share a block and, where the state is long,
+        // a pass of jump_words(N) state words is a block of its own
         const size_t pw = ((size_t)D + 31) / 32;
         Bs.emplace_back();
-        std::vector<JumpItem> &B = Bs.back();
-        std::vector<uint64_t> polys((size_t)g.C);
+        std::vector<JumpBlock> &B = Bs.back();
+        const uint64_t polys = (uint64_t)(uintptr_t)(ws + poly_off);
         for (int k = 1; k < g.C; ++k) {
             const uint64_t c = g.c0 + (uint64_t)k - 1;
-            polys[(size_t)k] = (uint64_t)(uintptr_t)(ws + poly_off);
             std::memcpy(at(poly_off), g.sj->g[(size_t)c - 1].data(), pw * 4);
             poly_off += pw * 4;
         }
-        for (int m0 = 0; m0 < N; m0 += JUMP_OUT_WORDS) {
-            for (int k = 1; k < g.C; ++k) {
-                JumpItem j;
+        for (int m0 = 0; m0 < N; m0 += jump_words(N)) {
+            for (int k = 1; k < g.C; k += per_block) {
+                JumpBlock j;
                 j.raw = (uint64_t)(uintptr_t)(raw + m0);
-                j.poly = polys[(size_t)k];
+                j.poly = polys + (uint64_t)(k - 1) * pw * 4;
                 j.out = (uint64_t)(uintptr_t)(js + (size_t)k * N + (size_t)m0);
+                j.poly_stride = (uint32_t)pw;
+                j.out_stride = (uint32_t)N;
                 j.nbits = (uint32_t)D;
-                j.m = (uint32_t)std::min(JUMP_OUT_WORDS, N - m0);
+                j.m = (uint32_t)std::min(jump_words(N), N - m0);
+                j.n_jumps = (uint32_t)std::min(per_block, g.C - k);
+                j.dep = 0;  // set when the prefixes are ordered
                 B.push_back(j);
-            }
-            while (B.size() % JUMP_BLOCK) {  // pad this pass's last block
-                JumpItem z;
-                std::memset(&z, 0, sizeof z);
-                B.push_back(z);
             }
         }
         // C: segments; every one but the last checks its end state against
@@ -898,12 +913,10 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
     std::memset(at(L.off_pflag), 0, A.size() * 4);
     size_t nb = 0;
     for (size_t i = A.size(); i-- > 0;) {
-        const std::vector<JumpItem> &B = Bs[std::get<2>(A[i])];
-        for (size_t j = 0; j < B.size(); j += JUMP_BLOCK, ++nb) {
-            std::memcpy(at(L.off_B) + nb * JUMP_BLOCK * sizeof(JumpItem), &B[j],
-                        JUMP_BLOCK * sizeof(JumpItem));
-            ((uint32_t *)at(L.off_jdep))[nb] = (uint32_t)i;
-        }
+        std::vector<JumpBlock> &B = Bs[std::get<2>(A[i])];
+        for (JumpBlock &j : B) j.dep = (uint32_t)i;
+        std::memcpy(at(L.off_B) + nb * sizeof(JumpBlock), B.data(), B.size() * sizeof(JumpBlock));
+        nb += B.size();
     }
     // Segment list, longest first.  Overlapped (whole requests beside the
     // prefix and jump launch): the segments of split requests first, then
@@ -925,14 +938,13 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
     }
     if (!F.empty()) std::memcpy(at(L.off_F), F.data(), F.size() * sizeof(BatchItem));
     w.nA = (uint32_t)A.size();
-    w.nB = (uint32_t)(nb * JUMP_BLOCK);
+    w.nB = (uint32_t)nb;
     w.nC = (uint32_t)C.size();
     w.nF = (uint32_t)F.size();
     w.off_A = L.off_A;
     w.off_B = L.off_B;
     w.off_C = L.off_C;
     w.off_F = L.off_F;
-    w.off_jdep = L.off_jdep;
     w.off_pflag = L.off_pflag;
     w.nCs = (uint32_t)(split_lists ? n_seg : C.size());
     w.overlap = split_lists;
@@ -968,7 +980,7 @@ static int overlap_groups(const ParamSet &ps, const mtgp_tuning &t) {
         hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) !=
             hipSuccess)
         return 0;
-    if (!wg_lds || (size_t)g * wg_lds + prefix_jump_lds_bytes() > (size_t)lds_cu) return 0;
+    if (!wg_lds || (size_t)g * wg_lds + prefix_jump_lds_bytes(ps.N) > (size_t)lds_cu) return 0;
     return g;
 }
 

@@ -60,8 +60,8 @@ struct WsState {
     std::mutex mu;
     Staging stage;
     uint64_t sig = 0;          // plan signature, 0 = no plan
-    uint32_t nA = 0, nB = 0, nC = 0, nF = 0;  // prefix, jump, segment, check items
-    size_t off_A = 0, off_B = 0, off_C = 0, off_F = 0, off_jdep = 0, off_pflag = 0;
+    uint32_t nA = 0, nB = 0, nC = 0, nF = 0;  // prefix items, jump blocks, segments, checks
+    size_t off_A = 0, off_B = 0, off_C = 0, off_F = 0, off_pflag = 0;
     // overlap: the plan's whole requests (after the nCs segments of split
     // requests in the segment list) start on `aux` beside the prefix and
     // jump launch, with at most overlap_groups workgroups per CU

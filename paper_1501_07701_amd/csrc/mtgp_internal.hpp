@@ -103,26 +103,36 @@ constexpr int HDR_W_CLAIM = 24;
 constexpr size_t HDR_STAMP_BYTE = 64;
 constexpr size_t HDR_BYTES = 256;
 
-// Jump evaluation item (32 bytes): out[m] = XOR_{i < nbits, g_i = 1}
-// raw[1 + i + m] for m < m_count.
-// Jump items are launched in blocks of JUMP_BLOCK: the items of a block
-// share raw, nbits and m (one stream); null items (out == 0) pad a block and
-// the first item of a block is never null.
-constexpr int JUMP_BLOCK = 4;
-// Output words one jump item evaluates in a single pass over its
-// coefficients; longer states are split into items of at most this many
-// words (item p covers words p * JUMP_OUT_WORDS onwards, its raw pointer
-// moved by as many words), so the passes of one jump run on different
-// workgroups at once.
-constexpr int JUMP_OUT_WORDS = 512;
-struct JumpItem {
-    uint64_t raw;     // words x_0, x_1, ... of a stream (at least nbits + m + 1)
-    uint64_t poly;    // coefficients g_0 .. g_{nbits-1}, 32 per uint32 word
-    uint64_t out;     // m words; 0 = padding
+// Jump block (48 bytes): up to JUMP_BLOCK jumps of one stream, each
+// out_j[m] = XOR_{i < nbits, g_j,i = 1} raw[1 + i + m] for m < this block's m.
+// A state longer than jump_words(N) is covered by several blocks (pass p
+// takes the words from p * jump_words(N) on, its raw and out pointers moved
+// by as many), so that the passes of a jump run on different workgroups.
+constexpr int JUMP_BLOCK = 8;
+struct JumpBlock {
+    uint64_t raw;          // words x_0, x_1, ... of a stream (nbits + m + 1 of them)
+    uint64_t poly;         // jump j's coefficients, 32 per word, at poly + j * poly_stride;
+                           // zero from nbits up to the end of the last word
+    uint64_t out;          // jump j's m words at out + j * out_stride
+    uint32_t poly_stride;  // words, ceil(nbits / 32)
+    uint32_t out_stride;   // words
     uint32_t nbits;
     uint32_t m;
+    uint32_t n_jumps;      // 1 .. JUMP_BLOCK
+    uint32_t dep;          // index of the prefix item that writes raw
 };
-static_assert(sizeof(JumpItem) == 32, "JumpItem layout");
+static_assert(sizeof(JumpBlock) == 48, "JumpBlock layout");
+// Tiles of 128 output words a block evaluates at once, and the words of a
+// pass: the state cut evenly into as few passes as four tiles allow (three
+// at N = 351 and 726, where they fit better).
+constexpr int JUMP_TILE = 128;
+constexpr int jump_tiles(int N) { return N <= 128 ? 1 : N <= 768 ? 3 : 4; }
+constexpr int jump_passes(int N) {
+    return (N + JUMP_TILE * jump_tiles(N) - 1) / (JUMP_TILE * jump_tiles(N));
+}
+constexpr int jump_words(int N) {
+    return ((N + jump_passes(N) - 1) / jump_passes(N) + 3) / 4 * 4;
+}
 
 struct LaunchArgs {
     const uint32_t *params;
@@ -150,19 +160,21 @@ struct VariantInfo {
 int variant_count(int n_words, VariantInfo *out, int max_out);
 hipError_t launch_variant(int n_words, int tps, int k, int wpb, const LaunchArgs &a,
                           bool *found);
-hipError_t launch_jump(const JumpItem *items, uint32_t n_items, int num_cus, hipStream_t s);
+// Jump blocks alone (their raw words are there), for state length n_words.
+hipError_t launch_jump(int n_words, const JumpBlock *blocks, uint32_t n_blocks, int num_cus,
+                       hipStream_t s);
 // Persistent launches of the prefix kernel (items may carry MODE_RAW) and
 // of the request-check kernel (MODE_FIXUP items) for state length n_words
 // (one wave per item; a.win_below applies).
 hipError_t launch_prefix(int n_words, const LaunchArgs &a);
 // LDS bytes of one prefix-and-jump workgroup.
-size_t prefix_jump_lds_bytes();
-// Prefix items (nP, one wave each) and jump blocks (nJ items in blocks of
-// JUMP_BLOCK; block b waits for pflag[jdep[b]]) in one persistent launch.
+size_t prefix_jump_lds_bytes(int n_words);
+// Prefix items (nP, one wave each) and jump blocks (nJ; block b waits for
+// pflag[b.dep]) in one persistent launch.
 hipError_t launch_prefix_jumps(int n_words, const BatchItem *prefix, uint32_t nP,
-                               const JumpItem *jumps, uint32_t nJ, const uint32_t *jdep,
-                               uint32_t *pflag, const uint32_t *params, uint32_t *hdr,
-                               uint32_t win_below, int num_cus, hipStream_t s);
+                               const JumpBlock *jumps, uint32_t nJ, uint32_t *pflag,
+                               const uint32_t *params, uint32_t *hdr, uint32_t win_below,
+                               int num_cus, hipStream_t s);
 hipError_t launch_check(int n_words, const LaunchArgs &a);
 int variant_slots_per_cu(int n_words, int tps, int k, int wpb);
 hipError_t launch_seed(const uint32_t *params, uint32_t *states, uint32_t stride,

@@ -66,6 +66,10 @@ hipError_t scratch_address(void **out) {
 template <typename T>
 using gptr = __attribute__((address_space(1))) T *;
 
+// Pointer into LDS (address space 3).
+template <typename T>
+using lptr = __attribute__((address_space(3))) T *;
+
 // a ^ b ^ c in one VALU operation (v_bitop3_b32 with truth table 0x96, the
 // odd-parity function of its three inputs); hipcc keeps XOR chains as
 // two-input operations.
@@ -667,132 +671,254 @@ check_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__ 
                                  plain);
 }
 
-// Jump evaluation: out[m] = XOR over the set bits i < D of g of r[i+m] with
-// r[n] = raw[1+n], for m < M.  Items come in blocks of JUMP_WAVES: one
-// workgroup per block, one wave per item; the items of a block use the same
-// words r (same stream, D and M) and null items (out == 0) only pad a block.
-// Coefficients are taken four at a time: for a nibble value v of g at
-// coefficients 4c..4c+3 the wave adds Q_v[4c+m], where
-// Q_v[n] = XOR over the set bits j of v of r[n+j].  The workgroup builds the
-// 15 planes Q_1..Q_15 for a chunk of JUMP_CH coefficients and JUMP_MT outputs
-// in LDS once, and every wave of the block reads them: per output word one
-// LDS read per nibble instead of one per set bit.  Plane 0 stays zero, so
-// the lookups are branch-free and several nibbles' reads are in flight.
-// Lane l owns output words 4l..4l+3 (+256 j) of a pass and reads them as one
-// 16-byte LDS access per nibble (4c + 4l is a multiple of 4).
-constexpr int JUMP_WAVES = JUMP_BLOCK;
-constexpr int JUMP_CH = 256;    // coefficients per chunk (multiple of 32)
-constexpr int JUMP_JA = 8;      // output words per lane per pass
-constexpr int JUMP_MT = 64 * JUMP_JA;
-constexpr int JUMP_PL = JUMP_CH + JUMP_MT;  // plane length (words)
-static_assert(JUMP_MT == JUMP_OUT_WORDS, "the planner splits jumps into passes of JUMP_MT words");
-constexpr int JUMP_LDS_BYTES = 16 * JUMP_PL * 4;
+// Jump evaluation: out_j[m] = XOR over the set bits i < D of g_j of r[i+m]
+// with r[n] = raw[1+n], for m < M: the product of a binary Hankel matrix of
+// words with the coefficient vectors of the block's jumps.
+//
+// Outputs are cut into T tiles of 128 words and coefficients into chunks of
+// T parts of 128, so that a chunk is a T x T block matrix whose block (a, b)
+// is the Hankel block R_{a+b} of words r[128 (a+b) ..].  With
+//   M_ab = R_{a+b} (g_a + g_b)   and   D_a = (sum over b of R_{a+b}) g_a
+// every output tile is y_a = D_a + the sum over b != a of M_ab, and M_ab
+// serves y_a and y_b: T (T+1) / 2 block products instead of T^2.
+//
+// A block product takes its coefficients four at a time: for a nibble value
+// v of the coefficients 4c..4c+3 a jump adds Q_v[4c+m], where Q_v[n] is the
+// XOR over the set bits j of v of w[n+j], w the 256 words of the block (for
+// D_a the XOR of T such runs).  The workgroup builds the planes Q_1..Q_15
+// in LDS (plane 0 stays zero, so lookups are branch-free) while its waves
+// look up the previous product's; a half-wave covers a tile's 128 words of
+// one jump, four words per lane and 16-byte read, two nibbles per
+// three-input XOR.  Where the block holds few jumps, two or four half-waves
+// share a jump's nibbles and are summed at the end.
+//
+// Bound by the 16-byte LDS reads and the vector work around them (four
+// operations per read): the prefix-and-jump launch of 128 x 2^24 mexp-11213
+// outputs takes 464-520 us (646-750 with T^2 block products over 512-word
+// tiles), of 4096 x 2^20 mexp-23209 490 us (650).
+constexpr int JUMP_WAVES = 4;
+constexpr int JUMP_PLANE = 2 * JUMP_TILE;                 // plane length (words)
+constexpr int JUMP_PLANES_WORDS = 16 * JUMP_PLANE;        // one product's planes
+static_assert(JUMP_BLOCK == 2 * JUMP_WAVES, "one jump per half-wave");
+__host__ __device__ constexpr int jump_lds_words(int T) {
+    // two sets of planes, two chunks of 2T tiles of words
+    return 2 * JUMP_PLANES_WORDS + 2 * 2 * T * JUMP_TILE;
+}
 
 typedef uint32_t jv4 __attribute__((ext_vector_type(4)));
 
-template <int JA>
-__device__ __forceinline__ void jump_pass(gptr<const uint32_t> r, gptr<const uint32_t> g,
-                                          uint32_t *__restrict__ out, bool active, uint32_t D,
-                                          uint32_t rlen, uint32_t m0, uint32_t mt,
-                                          uint32_t *__restrict__ planes, uint32_t lane) {
-    jv4 acc[JA];
+// 16 bytes of the plane that bits s .. s+3 of `bits` name, at LDS address
+// col + off in plane 0.
+__device__ __forceinline__ jv4 plane_read(uint32_t col, uint32_t bits, int s, int off) {
+    const uint32_t v = s >= 10 ? bits >> (s - 10) : bits << (10 - s);
+    return *reinterpret_cast<lptr<const jv4>>((uintptr_t)(((v & 0x3C00u) | col) + off));
+}
+
+// WPP: coefficient words (of the four of a part) one half-wave takes.
+template <int T, int WPP>
+__device__ __forceinline__ void jump_block(const JumpBlock &jb, uint32_t *__restrict__ lds,
+                                           uint32_t wave, uint32_t lane) {
+    constexpr int P = T * (T + 1) / 2;
+    constexpr uint32_t PARTS = 4 / WPP;
+    constexpr uint32_t CHUNK = T * JUMP_TILE;             // coefficients per chunk
+    constexpr uint32_t STAGE = 2 * T * JUMP_TILE;         // words a chunk reads
+    uint32_t *planes = lds;
+    uint32_t *stage = lds + 2 * JUMP_PLANES_WORDS;
+    const uint32_t tid = wave * 64 + lane, l32 = lane & 31u;
+    const uint32_t worker = 2 * wave + (lane >> 5);
+    const uint32_t jump = worker / PARTS, part = worker % PARTS;
+    const bool wave_active = (2 * wave) / PARTS < jb.n_jumps;  // uniform
+    gptr<const uint32_t> r = (gptr<const uint32_t>)(reinterpret_cast<const uint32_t *>(jb.raw)) + 1;
+    gptr<const uint32_t> g = (gptr<const uint32_t>)(reinterpret_cast<const uint32_t *>(jb.poly)) +
+                             (uint64_t)(jump < jb.n_jumps ? jump : 0u) * jb.poly_stride +
+                             part * WPP;
+    const uint32_t pw = jb.poly_stride, rlen = jb.nbits + jb.m;
+    const uint32_t n_chunks = (jb.nbits + CHUNK - 1) / CHUNK;
+
+    uint32_t raw[T];                                      // this thread's words of a chunk to come
+    auto load_raw = [&](uint32_t c) {
+        gptr<const uint32_t> p = r + c * CHUNK + tid;
+        if (c * CHUNK + STAGE <= rlen) {
 #pragma unroll
-    for (int j = 0; j < JA; ++j) acc[j] = jv4{0u, 0u, 0u, 0u};
-    for (uint32_t i0 = 0; i0 < D; i0 += JUMP_CH) {
-        const uint32_t ch = (D - i0) < (uint32_t)JUMP_CH ? (D - i0) : (uint32_t)JUMP_CH;
-        const uint32_t L = ch + mt;
-        const uint32_t base = i0 + m0;
-        const uint32_t nw = (ch + 31) / 32;
-        // this chunk's coefficient words, one per lane, fetched early
-        const uint32_t gv = (active && lane < nw) ? g[(i0 >> 5) + lane] : 0u;
-        __syncthreads();  // every wave is done with the previous chunk's planes
-        for (uint32_t t = threadIdx.x; t < L; t += 64 * JUMP_WAVES) {
-            const uint32_t n = base + t;
-            uint32_t w[4];
+            for (int k = 0; k < T; ++k) raw[k] = p[256 * k];
+        } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) w[j] = (n + j < rlen) ? r[n + j] : 0u;
-            uint32_t q[16];
-            q[0] = 0;
-#pragma unroll
-            for (int v = 1; v < 16; ++v) {
-                const int low = v & -v;
-                const int bit = low == 1 ? 0 : (low == 2 ? 1 : (low == 4 ? 2 : 3));
-                q[v] = q[v & (v - 1)] ^ w[bit];
-                planes[v * JUMP_PL + t] = q[v];
+            for (int k = 0; k < T; ++k) {
+                raw[k] = 0u;
+                if (c * CHUNK + tid + 256u * k < rlen) raw[k] = p[256 * k];
             }
         }
-        __syncthreads();
-        if (active) {
-            for (uint32_t cw = 0; cw < nw; ++cw) {
-                uint32_t bits = __builtin_amdgcn_readlane(gv, cw);
-                if (cw == nw - 1 && (ch & 31)) bits &= (1u << (ch & 31)) - 1u;
-                const uint32_t *col = planes + 32 * cw + 4 * lane;
-                // two nibbles per three-input XOR
+    };
+    auto store_raw = [&](uint32_t c) {
 #pragma unroll
-                for (int k = 0; k < 8; k += 2) {
-                    const uint32_t v0 = (bits >> (4 * k)) & 15u;
-                    const uint32_t v1 = (bits >> (4 * k + 4)) & 15u;
-                    const uint32_t *s0 = col + v0 * JUMP_PL + 4 * k;
-                    const uint32_t *s1 = col + v1 * JUMP_PL + 4 * k + 4;
+        for (int k = 0; k < T; ++k) stage[(c & 1u) * STAGE + tid + 256u * k] = raw[k];
+    };
+    uint32_t cw[T][WPP], cn[T][WPP];                      // coefficients: this chunk's, the next's
+    auto load_coeffs = [&](uint32_t c) {
+        gptr<const uint32_t> p = g + c * (CHUNK / 32);
+        if ((c + 1) * (CHUNK / 32) <= pw) {
 #pragma unroll
-                    for (int j = 0; j < JA; ++j) {
-                        const jv4 a = *reinterpret_cast<const jv4 *>(s0 + 256 * j);
-                        const jv4 b = *reinterpret_cast<const jv4 *>(s1 + 256 * j);
+            for (int a = 0; a < T; ++a)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) acc[j][e] = xor3(acc[j][e], a[e], b[e]);
+                for (int e = 0; e < WPP; ++e) cn[a][e] = p[4 * a + e];
+        } else {
+#pragma unroll
+            for (int a = 0; a < T; ++a)
+#pragma unroll
+                for (int e = 0; e < WPP; ++e) {
+                    cn[a][e] = 0u;
+                    if (c * (CHUNK / 32) + 4u * a + part * WPP + e < pw) cn[a][e] = p[4 * a + e];
+                }
+        }
+    };
+    const uint32_t m1 = wave & 1u ? ~0u : 0u, m2 = wave & 2u ? ~0u : 0u;
+    // planes 4 wave .. 4 wave + 3 of product (a, b) of chunk c; lane i makes
+    // the words 4i .. 4i+3 of each (the last four are never read)
+    auto build = [&](uint32_t c, int a, int b, uint32_t *pl) {
+        if (lane == 63u) return;
+        const jv4 *src = reinterpret_cast<const jv4 *>(stage + (c & 1u) * STAGE) + lane;
+        constexpr int TV = JUMP_TILE / 4;
+        jv4 lo, hi;
+        if (a != b) {
+            lo = src[(a + b) * TV];
+            hi = src[(a + b) * TV + 1];
+        } else {
+            lo = src[a * TV];
+            hi = src[a * TV + 1];
+#pragma unroll
+            for (int k = 1; k < T; ++k) {
+                lo ^= src[(a + k) * TV];
+                hi ^= src[(a + k) * TV + 1];
+            }
+        }
+        const jv4 w1 = {lo[1], lo[2], lo[3], hi[0]}, w2 = {lo[2], lo[3], hi[0], hi[1]},
+                  w3 = {lo[3], hi[0], hi[1], hi[2]};
+        const jv4 h = (w2 & m1) ^ (w3 & m2);
+        jv4 *dst = reinterpret_cast<jv4 *>(pl + 4 * wave * JUMP_PLANE) + lane;
+        dst[0] = h;
+        dst[JUMP_PLANE / 4] = h ^ lo;
+        dst[2 * (JUMP_PLANE / 4)] = h ^ w1;
+        dst[3 * (JUMP_PLANE / 4)] = h ^ lo ^ w1;
+    };
+
+    jv4 acc[T];
+#pragma unroll
+    for (int a = 0; a < T; ++a) acc[a] = jv4{0u, 0u, 0u, 0u};
+    load_raw(0);
+    load_coeffs(0);
+    __syncthreads();                                      // the previous block's LDS is free
+    store_raw(0);
+    if (n_chunks > 1) load_raw(1);
+    __syncthreads();
+    build(0, 0, 0, planes);
+    uint32_t flip = 0;                                    // planes of the product looked up next
+    for (uint32_t c = 0; c < n_chunks; ++c) {
+#pragma unroll
+        for (int a = 0; a < T; ++a)
+#pragma unroll
+            for (int e = 0; e < WPP; ++e) cw[a][e] = cn[a][e];
+        const bool more = c + 1 < n_chunks;
+        if (more) {
+            // stage[(c+1) & 1] was last read before the previous barrier
+            store_raw(c + 1);
+            load_coeffs(c + 1);
+            if (c + 2 < n_chunks) load_raw(c + 2);
+        }
+#pragma unroll
+        for (int a = 0; a < T; ++a) {
+#pragma unroll
+            for (int b = a; b < T; ++b) {
+                uint32_t *now = planes + flip;
+                flip ^= (uint32_t)JUMP_PLANES_WORDS;
+                __syncthreads();  // `now` is built, the other set no longer read
+                if (b + 1 < T) build(c, a, b + 1, planes + flip);
+                else if (a + 1 < T) build(c, a + 1, a + 1, planes + flip);
+                else if (more) build(c + 1, 0, 0, planes + flip);
+                if (wave_active) {
+                    // LDS byte address of the half-wave's first lookup in plane 0;
+                    // plane v lies v << 10 bytes on, bits that are zero here (the
+                    // planes start at LDS address 0 and 16 KB)
+                    const uint32_t col = (uint32_t)(uintptr_t)(lptr<uint32_t>)now + 16u * l32 +
+                                         part * (WPP * 128);
+                    jv4 y = jv4{0u, 0u, 0u, 0u};
+#pragma unroll
+                    for (int e = 0; e < WPP; ++e) {
+                        const uint32_t bits = a == b ? cw[a][e] : cw[a][e] ^ cw[b][e];
+                        jv4 q[8];  // eight reads in flight
+#pragma unroll
+                        for (int k = 0; k < 8; ++k)
+                            q[k] = plane_read(col, bits, 4 * k, 128 * e + 16 * k);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int k = 0; k < 8; k += 2)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) y[i] = xor3(y[i], q[k][i], q[k + 1][i]);
                     }
+                    acc[a] ^= y;
+                    if (a != b) acc[b] ^= y;
                 }
             }
         }
     }
-    if (active) {
+    uint32_t *out = reinterpret_cast<uint32_t *>(jb.out);
+    if constexpr (PARTS == 1) {
+        if (jump < jb.n_jumps) {
+            gptr<uint32_t> o = (gptr<uint32_t>)(out + (uint64_t)jump * jb.out_stride);
 #pragma unroll
-        for (int j = 0; j < JA; ++j) {
+            for (int a = 0; a < T; ++a)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const uint32_t m = 4 * lane + 256 * j + e;
-                if (m < mt) out[m0 + m] = acc[j][e];
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t m = JUMP_TILE * a + 4 * l32 + i;
+                    if (m < jb.m) o[m] = acc[a][i];
+                }
+        }
+    } else {
+        __syncthreads();                                  // the planes are no longer read
+        jv4 *sum = reinterpret_cast<jv4 *>(planes);
+#pragma unroll
+        for (int a = 0; a < T; ++a) sum[(worker * T + a) * (JUMP_TILE / 4) + l32] = acc[a];
+        __syncthreads();
+        const uint32_t *w = planes;
+        for (uint32_t j = 0; j < jb.n_jumps; ++j) {
+            gptr<uint32_t> o = (gptr<uint32_t>)(out + (uint64_t)j * jb.out_stride);
+            for (uint32_t m = tid; m < jb.m; m += 64 * JUMP_WAVES) {
+                uint32_t v = 0;
+#pragma unroll
+                for (uint32_t k = 0; k < PARTS; ++k) v ^= w[(j * PARTS + k) * CHUNK + m];
+                o[m] = v;
             }
         }
     }
 }
 
-// One block of JUMP_WAVES jump items (one wave each), planes in LDS.
-__device__ __forceinline__ void jump_block(const JumpItem *__restrict__ items, uint32_t n_items,
-                                           uint32_t blk, uint32_t *__restrict__ planes,
-                                           uint32_t wave, uint32_t lane) {
-    const JumpItem lead = items[blk * JUMP_WAVES];
-    const uint32_t mine = blk * JUMP_WAVES + wave;
-    JumpItem jit = lead;
-    jit.out = 0;
-    if (mine < n_items) jit = items[mine];
-    const bool active = jit.out != 0;
-    gptr<const uint32_t> r = (gptr<const uint32_t>)(reinterpret_cast<const uint32_t *>(lead.raw)) + 1;
-    gptr<const uint32_t> g = (gptr<const uint32_t>)(reinterpret_cast<const uint32_t *>(jit.poly));
-    uint32_t *out = reinterpret_cast<uint32_t *>(jit.out);
-    const uint32_t D = lead.nbits, M = lead.m, rlen = lead.nbits + lead.m;
-    for (uint32_t m0 = 0; m0 < M; m0 += JUMP_MT) {
-        const uint32_t mt = (M - m0) < (uint32_t)JUMP_MT ? (M - m0) : (uint32_t)JUMP_MT;
-        switch ((mt + 255) / 256) {
-#define MTGP_JP(JA) \
-    case JA: jump_pass<JA>(r, g, out, active, D, rlen, m0, mt, planes, lane); break;
-            MTGP_JP(1) MTGP_JP(2)
-#undef MTGP_JP
-            default: break;
-        }
-    }
+// Half-waves per jump by the jumps of the block, whose fields are made
+// wave-uniform explicitly (they are loaded from writable memory).
+template <int T>
+__device__ __forceinline__ void jump_any(const JumpBlock &b, uint32_t *__restrict__ lds,
+                                         uint32_t wave, uint32_t lane) {
+    JumpBlock jb;
+    jb.raw = uniform64(b.raw);
+    jb.poly = uniform64(b.poly);
+    jb.out = uniform64(b.out);
+    jb.poly_stride = __builtin_amdgcn_readfirstlane(b.poly_stride);
+    jb.out_stride = __builtin_amdgcn_readfirstlane(b.out_stride);
+    jb.nbits = __builtin_amdgcn_readfirstlane(b.nbits);
+    jb.m = __builtin_amdgcn_readfirstlane(b.m);
+    jb.n_jumps = __builtin_amdgcn_readfirstlane(b.n_jumps);
+    if (jb.n_jumps <= 2u) jump_block<T, 1>(jb, lds, wave, lane);
+    else if (jb.n_jumps <= 4u) jump_block<T, 2>(jb, lds, wave, lane);
+    else jump_block<T, 4>(jb, lds, wave, lane);
 }
 
 // Jump evaluation alone (the planning checks of jump-ahead polynomials).
+template <int T>
 __global__ void __launch_bounds__(64 * JUMP_WAVES)
-jump_kernel(const JumpItem *__restrict__ items, uint32_t n_items) {
-    extern __shared__ uint32_t planes[];
+jump_kernel(const JumpBlock *__restrict__ blocks, uint32_t n_blocks) {
+    extern __shared__ uint32_t lds[];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t n_blocks = (n_items + JUMP_WAVES - 1) / JUMP_WAVES;
-    for (uint32_t t = threadIdx.x; t < (uint32_t)JUMP_PL; t += 64 * JUMP_WAVES) planes[t] = 0u;
     for (uint32_t blk = blockIdx.x; blk < n_blocks; blk += gridDim.x)
-        jump_block(items, n_items, blk, planes, wave, lane);
+        jump_any<T>(blocks[blk], lds, wave, lane);
 }
 
 // Waits (a whole wave, every lane reading the same flag) until *flag is
@@ -824,25 +950,27 @@ struct PJArgs {
     const uint32_t *params;
     const BatchItem *prefix;  // nP prefix items
     uint32_t nP;
-    const JumpItem *jumps;    // nJ jump items in blocks of JUMP_WAVES
+    const JumpBlock *jumps;   // nJ jump blocks
     uint32_t nJ;
-    const uint32_t *jdep;     // per block: index of its stream's prefix item
     uint32_t *pflag;          // per prefix item: set to 1 when its words are stored
     uint32_t *hdr;            // workspace header (claim counters, timeouts)
     uint32_t win_below;
 };
 
-constexpr int PJ_LDS_BYTES = JUMP_LDS_BYTES + 16;  // planes + claim word
+// LDS words: the prefix buffers of the waves, or a jump block's; then the
+// claim word.  No static LDS: the planes are read with 16-byte LDS loads,
+// and a static word would move the dynamic region to offset 4.
+template <int N>
+__host__ __device__ constexpr int pj_lds_words() {
+    const int pre = JUMP_WAVES * Core<N, 64, 4>::LDS_WORDS, jmp = jump_lds_words(jump_tiles(N));
+    return (pre > jmp ? pre : jmp) + 4;
+}
 
 template <int N>
 __global__ void __launch_bounds__(64 * JUMP_WAVES) pj_kernel(PJArgs a) {
     using C = Core<N, 64, 4>;
-    static_assert(JUMP_WAVES * C::LDS_WORDS * 4 <= JUMP_LDS_BYTES, "prefix buffers fit the planes");
-    // No static LDS: the planes are read with 16-byte LDS loads, and a
-    // static word would move the dynamic region to offset 4.  The claim
-    // broadcast word sits right after the planes.
     extern __shared__ uint32_t lds[];
-    uint32_t &s_claim = lds[JUMP_LDS_BYTES / 4];
+    uint32_t &s_claim = lds[pj_lds_words<N>() - 4];
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63u;
     uint32_t *buf = lds + wave * C::LDS_WORDS;
@@ -862,46 +990,45 @@ __global__ void __launch_bounds__(64 * JUMP_WAVES) pj_kernel(PJArgs a) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __hip_atomic_store(a.pflag + it, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    const uint32_t n_blocks = (a.nJ + JUMP_WAVES - 1) / JUMP_WAVES;
-    __syncthreads();  // every wave of this workgroup is done with its prefix buffer
-    for (uint32_t t = threadIdx.x; t < (uint32_t)JUMP_PL; t += 64 * JUMP_WAVES) lds[t] = 0u;
     while (true) {  // jump blocks, one per workgroup
-        __syncthreads();
+        __syncthreads();  // (first: every wave is done with its prefix buffer)
         if (threadIdx.x == 0) s_claim = atomicAdd(a.hdr + HDR_J_CLAIM, 1u);
         __syncthreads();
         const uint32_t blk = __builtin_amdgcn_readfirstlane(s_claim);
-        if (blk >= n_blocks) break;
-        if (wave == 0) wait_flag(a.pflag + a.jdep[blk], a.hdr + HDR_ERR, lane);
+        if (blk >= a.nJ) break;
+        const JumpBlock jb = a.jumps[blk];
+        const uint32_t dep = __builtin_amdgcn_readfirstlane(jb.dep);
+        if (wave == 0) wait_flag(a.pflag + dep, a.hdr + HDR_ERR, lane);
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        jump_block(a.jumps, a.nJ, blk, lds, wave, lane);
+        jump_any<jump_tiles(N)>(jb, lds, wave, lane);
     }
 }
 
 template <int N>
 static hipError_t launch_pj_n(const PJArgs &a, int num_cus, hipStream_t s) {
+    constexpr int lds = pj_lds_words<N>() * 4;
     static bool attr_set = false;  // benign race: idempotent attribute
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void *)pj_kernel<N>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           PJ_LDS_BYTES);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    const uint32_t work = a.nP + (a.nJ + JUMP_WAVES - 1) / JUMP_WAVES;
+    const uint32_t work = a.nP + a.nJ;
     int grid = (int)(work > 0 ? work : 1);
-    const int cap = num_cus * 3;  // three workgroups of 48 KB fit a CU's LDS
+    const int cap = num_cus * (160 * 1024 / lds);  // workgroups that fit the CUs' LDS
     if (grid > cap) grid = cap;
     (void)hipGetLastError();  // report this launch only
-    hipLaunchKernelGGL(pj_kernel<N>, dim3(grid), dim3(64 * JUMP_WAVES), PJ_LDS_BYTES, s, a);
+    hipLaunchKernelGGL(pj_kernel<N>, dim3(grid), dim3(64 * JUMP_WAVES), lds, s, a);
     return hipGetLastError();
 }
 
 hipError_t launch_prefix_jumps(int n_words, const BatchItem *prefix, uint32_t nP,
-                               const JumpItem *jumps, uint32_t nJ, const uint32_t *jdep,
-                               uint32_t *pflag, const uint32_t *params, uint32_t *hdr,
-                               uint32_t win_below, int num_cus, hipStream_t s) {
-    PJArgs a{params, prefix, nP, jumps, nJ, jdep, pflag, hdr, win_below};
+                               const JumpBlock *jumps, uint32_t nJ, uint32_t *pflag,
+                               const uint32_t *params, uint32_t *hdr, uint32_t win_below,
+                               int num_cus, hipStream_t s) {
+    PJArgs a{params, prefix, nP, jumps, nJ, pflag, hdr, win_below};
     switch (n_words) {
         case 101: return launch_pj_n<101>(a, num_cus, s);
         case 351: return launch_pj_n<351>(a, num_cus, s);
@@ -911,7 +1038,15 @@ hipError_t launch_prefix_jumps(int n_words, const BatchItem *prefix, uint32_t nP
     }
 }
 
-size_t prefix_jump_lds_bytes() { return PJ_LDS_BYTES; }
+size_t prefix_jump_lds_bytes(int n_words) {
+    switch (n_words) {
+        case 101: return 4 * pj_lds_words<101>();
+        case 351: return 4 * pj_lds_words<351>();
+        case 726: return 4 * pj_lds_words<726>();
+        case 1391: return 4 * pj_lds_words<1391>();
+        default: return 0;
+    }
+}
 
 // Seeding: one lane per stream runs the N-step initialisation recurrence, a
 // serial chain of a shift, an XOR and a 32-bit multiply-add per word.  The
@@ -1152,24 +1287,36 @@ int variant_slots_per_cu(int n_words, int tps, int k, int wpb) {
     return 0;
 }
 
-hipError_t launch_jump(const JumpItem *items, uint32_t n_items, int num_cus, hipStream_t s) {
-    if (n_items == 0) return hipSuccess;
+template <int T>
+static hipError_t launch_jump_t(const JumpBlock *blocks, uint32_t n_blocks, int num_cus,
+                                hipStream_t s) {
+    constexpr int lds = jump_lds_words(T) * 4;
     static bool attr_set = false;  // benign race: idempotent attribute
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute((const void *)jump_kernel,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           JUMP_LDS_BYTES);
+        hipError_t e = hipFuncSetAttribute((const void *)jump_kernel<T>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    int grid = (int)((n_items + JUMP_WAVES - 1) / JUMP_WAVES);
-    const int cap = num_cus * 3;  // three blocks of 48 KB planes fit a CU's LDS
-
+    int grid = (int)n_blocks;
+    const int cap = num_cus * (160 * 1024 / lds);  // workgroups that fit the CUs' LDS
     if (grid > cap) grid = cap;
     (void)hipGetLastError();  // report this launch only
-    hipLaunchKernelGGL(jump_kernel, dim3(grid), dim3(64 * JUMP_WAVES), JUMP_LDS_BYTES, s, items,
-                       n_items);
+    hipLaunchKernelGGL(jump_kernel<T>, dim3(grid), dim3(64 * JUMP_WAVES), lds, s, blocks,
+                       n_blocks);
     return hipGetLastError();
+}
+
+hipError_t launch_jump(int n_words, const JumpBlock *blocks, uint32_t n_blocks, int num_cus,
+                       hipStream_t s) {
+    if (n_blocks == 0) return hipSuccess;
+    switch (n_words) {
+        case 101: return launch_jump_t<jump_tiles(101)>(blocks, n_blocks, num_cus, s);
+        case 351: return launch_jump_t<jump_tiles(351)>(blocks, n_blocks, num_cus, s);
+        case 726: return launch_jump_t<jump_tiles(726)>(blocks, n_blocks, num_cus, s);
+        case 1391: return launch_jump_t<jump_tiles(1391)>(blocks, n_blocks, num_cus, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_seed(const uint32_t *params, uint32_t *states, uint32_t stride,
