@@ -306,6 +306,16 @@ static int generate_plain(const void *d_params, uint32_t *d_states, int stride, 
     a.persistent = false;
     a.num_cus = device_cus();
     a.stream = s;
+    // Few streams: two waves per SIMD (four where the state is long) do not
+    // fill the chip, so the dependent chain sets the time.  1024 mexp-44497
+    // streams of 12,289 words 65 us (75 by the batch kernel), 100 mexp-11213
+    // streams of 20,000 101 (113); 4096 mexp-3217 streams of 3,000 64 (61).
+    const int few = ps->N > 400 ? 16 : 8;
+    if (t.threads_per_stream == 64 && n_streams <= few * a.num_cus) {
+        a.win_below = (uint32_t)t.window_below_w;
+        const hipError_t e = launch_few(ps->N, a);
+        return e == hipSuccess ? MTGP_OK : hip_fail(e, "kernel launch");
+    }
     return launch_tuned(ps->N, t, a);
 }
 

@@ -167,6 +167,8 @@ hipError_t launch_jump(int n_words, const JumpBlock *blocks, uint32_t n_blocks, 
 // of the request-check kernel (MODE_FIXUP items) for state length n_words
 // (one wave per item; a.win_below applies).
 hipError_t launch_prefix(int n_words, const LaunchArgs &a);
+// Plain calls of few streams (one wave per stream, a.win_below applies).
+hipError_t launch_few(int n_words, const LaunchArgs &a);
 // LDS bytes of one prefix-and-jump workgroup.
 size_t prefix_jump_lds_bytes(int n_words);
 // Prefix items (nP, one wave each) and jump blocks (nJ; block b waits for

@@ -129,14 +129,23 @@ struct Core {
     static __device__ __forceinline__ uint32_t rec(const Step &p, const uint32_t *tbl,
                                                    uint32_t Y) {
         if constexpr (LIN) {
-            uint32_t r = (0u - (Y & 1u)) & p.rb0;
-            r ^= (0u - ((Y >> 1) & 1u)) & p.rb1;
-            r ^= (0u - ((Y >> 2) & 1u)) & p.rb2;
-            r ^= (0u - ((Y >> 3) & 1u)) & p.rb3;
-            return Y ^ r;
+            return rec_reg(p, Y);
         } else {
             return Y ^ tbl[Y & 15u];
         }
+    }
+
+    // The linear table's with a bit mask and a three-input operation
+    // (0x78: a ^ (b & c)) per basis word.
+    static __device__ __forceinline__ uint32_t rec_reg(const Step &p, uint32_t Y) {
+        uint32_t a = __builtin_amdgcn_bitop3_b32(Y, (uint32_t)__builtin_amdgcn_sbfe((int)Y, 0, 1),
+                                                 p.rb0, 0x78);
+        a = __builtin_amdgcn_bitop3_b32(a, (uint32_t)__builtin_amdgcn_sbfe((int)Y, 1, 1), p.rb1,
+                                        0x78);
+        a = __builtin_amdgcn_bitop3_b32(a, (uint32_t)__builtin_amdgcn_sbfe((int)Y, 2, 1), p.rb2,
+                                        0x78);
+        return __builtin_amdgcn_bitop3_b32(a, (uint32_t)__builtin_amdgcn_sbfe((int)Y, 3, 1), p.rb3,
+                                           0x78);
     }
 
     template <bool F32>
@@ -335,7 +344,88 @@ struct Core {
         }
     }
 
-    template <bool F32>
+    // The same window for a wave that runs alone or nearly so (plain calls
+    // of few streams, prefixes), where the dependent chain and not the work
+    // sets the time: the recursion table in registers (48 cycles an element
+    // instead of 100), lanes exchange words by shuffles, and tempering keeps
+    // four rows' LDS reads in flight.
+    template <bool F32, int E>
+    static __device__ __forceinline__ void steps_window_lat(const Step &p,
+                                                            const uint32_t *__restrict__ prm,
+                                                            uint32_t *__restrict__ buf,
+                                                            gptr<uint32_t> gout, gptr<uint32_t> raw,
+                                                            bool want_raw, uint64_t count,
+                                                            uint32_t &h, uint64_t &done,
+                                                            uint32_t lane) {
+        const uint32_t *tbl = buf + WBUF;
+        uint32_t *mats = buf + WBUF + 32 + 64;
+        const uint32_t W = p.W;
+        const uint32_t wn = prm[P_WIN_WN], q = prm[P_WIN_Q];
+        const uint32_t rounds = prm[P_WIN_ROUNDS];
+        for (uint32_t i = lane; i < rounds * WIN_MAT_WORDS; i += 64) mats[i] = prm[P_WIN_MAT + i];
+        const uint32_t r = lane / q, sub = lane - (lane / q) * q;
+        const bool lane_ok = r < W;
+        const uint32_t off0 = r + W * (sub * (uint32_t)E);  // the lane's first element
+        group_sync<TPS>();
+        while (done < count) {
+            const uint64_t rem = count - done;
+            const uint32_t wc = rem < wn ? (uint32_t)rem : wn;
+            maybe_compact<WBUF>(buf, h, wc, lane);
+            const uint32_t left = lane_ok && off0 < wc ? wc - off0 : 0u;  // words from off0 on
+            uint32_t X[E];
+#pragma unroll
+            for (int j = 0; j < E; ++j) {
+                const uint32_t idx = W * j < left ? h + off0 + W * j - N : h - N;
+                const uint32_t x0 = (buf[idx] & p.mask) ^ buf[idx + 1];
+                X[j] = x0 ^ (x0 << p.sh1);
+            }
+            uint32_t c = (sub == 0 && lane_ok) ? buf[h + r - W] : 0u;
+            if (rounds) {
+                uint32_t u = c;
+#pragma unroll
+                for (int j = 0; j < E; ++j) u = rec_reg(p, X[j] ^ (u >> p.sh2));
+                for (uint32_t k = 0; k < rounds; ++k) {
+                    const uint32_t d = 1u << k;
+                    const uint32_t w = (uint32_t)__shfl((int)u, (int)(sub >= d ? lane - d : lane), 64);
+                    const uint32_t y = mat_apply(mats + k * WIN_MAT_WORDS, w);
+                    if (sub >= d) u ^= y;
+                }
+                const uint32_t cin = (uint32_t)__shfl((int)u, (int)(sub > 0 ? lane - 1 : lane), 64);
+                if (sub > 0) c = cin;
+            }
+#pragma unroll
+            for (int j = 0; j < E; ++j) {
+                c = rec_reg(p, X[j] ^ (c >> p.sh2));
+                if (W * j < left) buf[h + off0 + W * j] = c;
+            }
+            group_sync<TPS>();
+            for (uint32_t p0 = 0; p0 < wc; p0 += 256) {
+                uint32_t x[4], o[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t pp = p0 + 64u * i + lane;
+                    const uint32_t at = h + (pp < wc ? pp : wc - 1u);
+                    x[i] = buf[at];
+                    o[i] = buf[at - W - 1];
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i) o[i] = temper<F32>(tbl, x[i], o[i]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t pp = p0 + 64u * i + lane;
+                    if (pp < wc) {
+                        gout[done + pp] = o[i];
+                        if (want_raw) raw[N + done + pp] = x[i];
+                    }
+                }
+            }
+            group_sync<TPS>();
+            h += wc;
+            done += wc;
+        }
+    }
+
+    template <bool F32, bool LAT>
     static __device__ __forceinline__ void steps_window(const Step &p,
                                                         const uint32_t *__restrict__ prm,
                                                         uint32_t *__restrict__ buf,
@@ -345,7 +435,12 @@ struct Core {
                                                         uint32_t lane) {
         switch (prm[P_WIN_E]) {
 #define MTGP_WE(E) \
-    case E: steps_window_e<F32, E>(p, prm, buf, gout, raw, want_raw, count, h, done, lane); break;
+    case E:                                                                                       \
+        if constexpr (LAT)                                                                        \
+            steps_window_lat<F32, E>(p, prm, buf, gout, raw, want_raw, count, h, done, lane);     \
+        else                                                                                      \
+            steps_window_e<F32, E>(p, prm, buf, gout, raw, want_raw, count, h, done, lane);       \
+        break;
             MTGP_WE(1) MTGP_WE(2) MTGP_WE(3) MTGP_WE(4)
             MTGP_WE(5) MTGP_WE(6) MTGP_WE(7) MTGP_WE(8)
 #undef MTGP_WE
@@ -456,8 +551,9 @@ struct Core {
 
     // Advance one stream by item.count outputs.  A MODE_VERIFY item that
     // ends in a state other than item.verify sets *fail.  RAW: the
-    // MODE_RAW word dump is compiled in (prefix kernels only).
-    template <bool F32, bool RAW>
+    // MODE_RAW word dump is compiled in (prefix kernels only); LAT: narrow
+    // streams take the window for a wave that runs nearly alone.
+    template <bool F32, bool RAW, bool LAT>
     static __device__ __forceinline__ void run(const uint32_t *__restrict__ prm,
                                                const BatchItem &item,
                                                uint32_t *__restrict__ buf, uint32_t lane,
@@ -498,7 +594,7 @@ struct Core {
         uint32_t h = N;  // buffer index of the next new word
         uint64_t done = 0;
         if (win) {
-            steps_window<F32>(p, prm, buf, gout, raw, want_raw, count, h, done, lane);
+            steps_window<F32, LAT>(p, prm, buf, gout, raw, want_raw, count, h, done, lane);
         } else if (TPS == 64 && p.W < 64) {
             if (lin)
                 steps_small<F32, true>(p, buf, tbl, gout, raw, want_raw, count, h, done, lane);
@@ -551,11 +647,10 @@ __device__ __forceinline__ uint32_t group_first(uint32_t v, uint32_t *slot) {
 
 // The work loop shared by the generation kernels: claim an item (or take
 // stream `it` in plain mode), run it, raise its completion flag.
-template <int N, int TPS, int K, int WPB, bool RAW>
+template <int N, int TPS, int K, int WPB, bool RAW, bool LAT>
 __device__ __forceinline__ void gen_body(const uint32_t *__restrict__ params,
                                          const BatchItem *__restrict__ items, uint32_t n_items,
-                                         uint32_t *__restrict__ counter,
-                                         uint32_t *__restrict__ err, uint32_t persistent,
+                                         uint32_t *__restrict__ counter, uint32_t persistent,
                                          uint32_t win_below, PlainArgs plain) {
     using C = Core<N, TPS, K>;
     extern __shared__ uint32_t lds[];
@@ -586,41 +681,15 @@ __device__ __forceinline__ void gen_body(const uint32_t *__restrict__ params,
             item.state_in = item.state_out = (uint64_t)(uintptr_t)row;
             item.raw = item.verify = item.rec = item.flag = 0;
         }
-        if (item.mode & MODE_FIXUP) {
-            // Request check, after every segment of the request has
-            // finished: if a segment started from a wrong jumped state (the
-            // stream's state lay outside the orbit its polynomial
-            // annihilates), regenerate the whole request in order from its
-            // start state and log it.  Record fields are loaded from
-            // writable memory, so they are made wave-uniform explicitly.
-            const ReqRec *rec = reinterpret_cast<const ReqRec *>(item.rec);
-            const uint32_t failed = __builtin_amdgcn_readfirstlane(
-                __hip_atomic_load(&rec->failed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-            item.count = 0;
-            if (failed) {
-                item.stream = __builtin_amdgcn_readfirstlane(rec->stream);
-                item.mode = __builtin_amdgcn_readfirstlane(rec->mode);
-                item.count = uniform64(rec->count);
-                item.out = uniform64(rec->out);
-                item.state_in = uniform64(rec->orig);
-                item.state_out = uniform64(rec->row);
-                item.raw = item.verify = 0;
-                if (lane == 0) {
-                    atomicAdd(err, 1u);
-                    const uint32_t slot = atomicAdd(err + 1, 1u);
-                    if (slot < (uint32_t)HDR_LOG_MAX) err[2 + slot] = item.stream;
-                }
-            }
-        }
         if (item.count > 0) {
             const uint32_t *prm = params + (uint64_t)item.stream * P_WORDS;
             uint32_t *fail = (item.mode & MODE_VERIFY)
                                  ? &reinterpret_cast<ReqRec *>(item.rec)->failed
                                  : nullptr;
             if (item.mode & MODE_F32)
-                C::template run<true, RAW>(prm, item, buf, lane, fail, win_below);
+                C::template run<true, RAW, LAT>(prm, item, buf, lane, fail, win_below);
             else
-                C::template run<false, RAW>(prm, item, buf, lane, fail, win_below);
+                C::template run<false, RAW, LAT>(prm, item, buf, lane, fail, win_below);
         }
         if (item.flag != 0) {
             // Publish completion of the request to the host: every lane's
@@ -639,36 +708,99 @@ __device__ __forceinline__ void gen_body(const uint32_t *__restrict__ params,
 template <int N, int TPS, int K, int WPB>
 __global__ void __launch_bounds__(TPS == 64 ? 64 * WPB : TPS)
 gen_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__ items,
-           uint32_t n_items, uint32_t *__restrict__ counter, uint32_t *__restrict__ err,
-           uint32_t persistent, uint32_t win_below, PlainArgs plain) {
-    gen_body<N, TPS, K, WPB, false>(params, items, n_items, counter, err, persistent, win_below,
-                                    plain);
+           uint32_t n_items, uint32_t *__restrict__ counter, uint32_t persistent,
+           uint32_t win_below, PlainArgs plain) {
+    gen_body<N, TPS, K, WPB, false, false>(params, items, n_items, counter, persistent,
+                                           win_below, plain);
+}
+
+// Plain calls of few streams: one wave per stream with room for longer runs
+// between compactions, and the latency-bound window.
+template <int N>
+__global__ void __launch_bounds__(256)
+few_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__ items,
+           uint32_t n_items, uint32_t *__restrict__ counter, uint32_t persistent,
+           uint32_t win_below, PlainArgs plain) {
+    gen_body<N, 64, 8, 4, false, true>(params, items, n_items, counter, persistent, win_below,
+                                       plain);
 }
 
 // Outputs per lane and step of the prefix kernel (the default tuning's).
 __host__ __device__ constexpr int prefix_k(int N) { return N <= 400 ? 4 : 8; }
 
-// Prefix items of split requests (the first D+1 outputs, dumping the raw
-// words the jump evaluation reads), and the word runs jump-ahead planning
-// takes its polynomials from: one wave per item, four waves per workgroup.
+// The word runs jump-ahead planning takes its polynomials from: one wave
+// per item, four waves per workgroup.
 template <int N>
 __global__ void __launch_bounds__(256)
 prefix_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__ items,
-              uint32_t n_items, uint32_t *__restrict__ counter, uint32_t *__restrict__ err,
-              uint32_t persistent, uint32_t win_below, PlainArgs plain) {
-    gen_body<N, 64, prefix_k(N), 4, true>(params, items, n_items, counter, err, persistent,
-                                          win_below, plain);
+              uint32_t n_items, uint32_t *__restrict__ counter, uint32_t persistent,
+              uint32_t win_below, PlainArgs plain) {
+    gen_body<N, 64, prefix_k(N), 4, true, true>(params, items, n_items, counter, persistent,
+                                                win_below, plain);
 }
 
-// Request checks of split requests (MODE_FIXUP items), after the segments:
-// usually no generation at all; a failed request is regenerated here.
+// Request checks of split requests (MODE_FIXUP items), after every segment
+// has finished.  If a segment started from a wrong jumped state (the
+// stream's state lay outside the orbit its polynomial annihilates), the
+// whole request is regenerated in order from its start state and logged.
+// That is rare, so a wave looks at `per_wave` requests at once, one per
+// lane (10,000 requests: 5 us against 107 us with a claim per request).
+// Record fields are loaded from writable memory, so they are made
+// wave-uniform explicitly.
 template <int N>
 __global__ void __launch_bounds__(256)
 check_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__ items,
-             uint32_t n_items, uint32_t *__restrict__ counter, uint32_t *__restrict__ err,
-             uint32_t persistent, uint32_t win_below, PlainArgs plain) {
-    gen_body<N, 64, 1, 4, false>(params, items, n_items, counter, err, persistent, win_below,
-                                 plain);
+             uint32_t n_items, uint32_t per_wave, uint32_t *__restrict__ err,
+             uint32_t win_below) {
+    using C = Core<N, 64, 1>;
+    extern __shared__ uint32_t lds[];
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t i = (blockIdx.x * 4 + wave) * per_wave + lane;
+    uint64_t rec_addr = 0, flag = 0;
+    uint32_t failed = 0;
+    if (lane < per_wave && i < n_items) {
+        rec_addr = items[i].rec;
+        flag = items[i].flag;
+        failed = __hip_atomic_load(&reinterpret_cast<const ReqRec *>(rec_addr)->failed,
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    uint64_t todo = __builtin_amdgcn_ballot_w64(failed != 0u);
+    while (todo) {
+        const int l = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const uint64_t addr = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane(
+                                   (int)(uint32_t)(rec_addr >> 32), l) << 32) |
+                              (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)rec_addr, l);
+        const ReqRec *rec = reinterpret_cast<const ReqRec *>(addr);
+        BatchItem item;
+        item.stream = __builtin_amdgcn_readfirstlane(rec->stream);
+        item.mode = __builtin_amdgcn_readfirstlane(rec->mode);
+        item.count = uniform64(rec->count);
+        item.out = uniform64(rec->out);
+        item.state_in = uniform64(rec->orig);
+        item.state_out = uniform64(rec->row);
+        item.raw = item.verify = 0;
+        if (lane == 0) {
+            atomicAdd(err, 1u);
+            const uint32_t slot = atomicAdd(err + 1, 1u);
+            if (slot < (uint32_t)HDR_LOG_MAX) err[2 + slot] = item.stream;
+        }
+        const uint32_t *prm = params + (uint64_t)item.stream * P_WORDS;
+        uint32_t *buf = lds + wave * C::LDS_WORDS;
+        if (item.mode & MODE_F32)
+            C::template run<true, false, false>(prm, item, buf, lane, nullptr, win_below);
+        else
+            C::template run<false, false, false>(prm, item, buf, lane, nullptr, win_below);
+    }
+    if (__builtin_amdgcn_ballot_w64(flag != 0)) {
+        // publish completion to the host, after every lane's stores
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+        group_sync<64>();
+        if (flag != 0)
+            __hip_atomic_store(reinterpret_cast<uint32_t *>(flag), 1u, __ATOMIC_RELEASE,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+    }
 }
 
 // Jump evaluation: out_j[m] = XOR over the set bits i < D of g_j of r[i+m]
@@ -982,9 +1114,9 @@ __global__ void __launch_bounds__(64 * JUMP_WAVES) pj_kernel(PJArgs a) {
         const BatchItem item = a.prefix[it];
         const uint32_t *prm = a.params + (uint64_t)item.stream * P_WORDS;
         if (item.mode & MODE_F32)
-            C::template run<true, true>(prm, item, buf, lane, nullptr, a.win_below);
+            C::template run<true, true, true>(prm, item, buf, lane, nullptr, a.win_below);
         else
-            C::template run<false, true>(prm, item, buf, lane, nullptr, a.win_below);
+            C::template run<false, true, true>(prm, item, buf, lane, nullptr, a.win_below);
         // every lane stores the flag: a lane-0-only store here lets the
         // compiler split the claim loop by lane
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
@@ -1132,8 +1264,8 @@ fill_kernel(u32x4 *__restrict__ out, uint64_t n_vec, uint32_t *__restrict__ tail
 
 // ------------------------------------------------------------- dispatch --
 
-typedef void (*GenFn)(const uint32_t *, const BatchItem *, uint32_t, uint32_t *, uint32_t *,
-                      uint32_t, uint32_t, PlainArgs);
+typedef void (*GenFn)(const uint32_t *, const BatchItem *, uint32_t, uint32_t *, uint32_t,
+                      uint32_t, PlainArgs);
 
 // Launches one of the generation kernels with the LDS of Core<N, TPS, K>
 // times the groups per workgroup; persistent launches fill every CU to its
@@ -1164,8 +1296,7 @@ static hipError_t launch_with(GenFn fn, bool *attr_set, const LaunchArgs &a) {
     PlainArgs plain{a.plain_states, a.plain_stride, a.plain_mode, a.plain_out, a.plain_count};
     (void)hipGetLastError();  // report this launch only
     hipLaunchKernelGGL(fn, dim3(grid), dim3(threads), lds, (hipStream_t)a.stream, a.params,
-                       a.items, a.n_items, a.counter, a.err, a.persistent ? 1u : 0u,
-                       a.win_below, plain);
+                       a.items, a.n_items, a.counter, a.persistent ? 1u : 0u, a.win_below, plain);
     return hipGetLastError();
 }
 
@@ -1183,8 +1314,42 @@ static hipError_t launch_prefix_n(const LaunchArgs &a) {
 
 template <int N>
 static hipError_t launch_check_n(const LaunchArgs &a) {
+    constexpr int lds = Core<N, 64, 1>::LDS_WORDS * 4 * 4;
+    static bool attr_set = false;  // benign race: idempotent attribute
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void *)check_kernel<N>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    // one request per wave up to two waves per SIMD, so that requests which
+    // do have to be regenerated run beside one another
+    const uint32_t waves = (uint32_t)(a.num_cus > 0 ? a.num_cus : 1) * 8u;
+    uint32_t per_wave = (a.n_items + waves - 1) / waves;
+    if (per_wave > 64u) per_wave = 64u;
+    if (per_wave < 1u) per_wave = 1u;
+    const uint32_t grid = (a.n_items + 4 * per_wave - 1) / (4 * per_wave);
+    (void)hipGetLastError();  // report this launch only
+    hipLaunchKernelGGL(check_kernel<N>, dim3(grid > 0 ? grid : 1), dim3(256), lds,
+                       (hipStream_t)a.stream, a.params, a.items, a.n_items, per_wave, a.err,
+                       a.win_below);
+    return hipGetLastError();
+}
+
+template <int N>
+static hipError_t launch_few_n(const LaunchArgs &a) {
     static bool attr_set = false;
-    return launch_with<N, 64, 1, 4>(check_kernel<N>, &attr_set, a);
+    return launch_with<N, 64, 8, 4>(few_kernel<N>, &attr_set, a);
+}
+
+hipError_t launch_few(int n_words, const LaunchArgs &a) {
+    switch (n_words) {
+        case 101: return launch_few_n<101>(a);
+        case 351: return launch_few_n<351>(a);
+        case 726: return launch_few_n<726>(a);
+        case 1391: return launch_few_n<1391>(a);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_prefix(int n_words, const LaunchArgs &a) {
