@@ -605,16 +605,22 @@ std::shared_ptr<WsState> ws_state(const void *d_ws, bool create) {
     return g_ws.front().second;
 }
 
+// Everything a captured graph's kernel arguments depend on: the item counts
+// and where the tables lie (the jump blocks' table is sized for two jumps a
+// block, so the counts alone do not give the offsets).
 struct GraphKey {
     const void *ws;
-    uint32_t nA, nB, nC;
+    uint32_t nA, nB, nC, nF;
+    size_t off_A, off_B, off_C, off_F, off_pflag;
     const void *params;
     int N, tps, k, wg, win, device;
     bool stamps, errs;
     bool operator<(const GraphKey &o) const {
-        return std::tie(ws, nA, nB, nC, params, N, tps, k, wg, win, device, stamps, errs) <
-               std::tie(o.ws, o.nA, o.nB, o.nC, o.params, o.N, o.tps, o.k, o.wg, o.win,
-                        o.device, o.stamps, o.errs);
+        return std::tie(ws, nA, nB, nC, nF, off_A, off_B, off_C, off_F, off_pflag, params, N,
+                        tps, k, wg, win, device, stamps, errs) <
+               std::tie(o.ws, o.nA, o.nB, o.nC, o.nF, o.off_A, o.off_B, o.off_C, o.off_F,
+                        o.off_pflag, o.params, o.N, o.tps, o.k, o.wg, o.win, o.device, o.stamps,
+                        o.errs);
     }
 };
 std::atomic<bool> g_stamps{false};  // phase timestamps in every batch call
@@ -1074,9 +1080,9 @@ int run_batch(const std::shared_ptr<ParamSet> &ps, const void *d_params, uint32_
 
     int dev = 0;
     (void)hipGetDevice(&dev);
-    GraphKey key{d_ws, w.nA, w.nB, w.nC, d_params, ps->N, t.threads_per_stream,
-                 t.outputs_per_lane, t.workgroup_size, t.window_below_w, dev, stamps,
-                 per_call_errors};
+    GraphKey key{d_ws, w.nA, w.nB, w.nC, w.nF, w.off_A, w.off_B, w.off_C, w.off_F, w.off_pflag,
+                 d_params, ps->N, t.threads_per_stream, t.outputs_per_lane, t.workgroup_size,
+                 t.window_below_w, dev, stamps, per_call_errors};
     std::lock_guard<std::mutex> lk(g_graph_mu);
     auto it = g_graphs.find(key);
     if (it == g_graphs.end()) {
