@@ -176,6 +176,15 @@ static void window_data(const mtgp_params &p, int N, uint32_t *b) {
             for (uint32_t v = 0; v < 16; ++v) t[k * 16 + v] = mat_vec(P, v << (4 * k));
         P = mat_mul(P, P);
     }
+    if (has_groups(N) && (64u >> group_log(W)) / W > 1u) {
+        P = mat_pow(M, GROUP_E);
+        for (uint32_t r = 0; r < (uint32_t)GROUP_ROUNDS; ++r) {
+            uint32_t *t = b + P_GRP_MAT + r * WIN_MAT_WORDS;
+            for (int k = 0; k < 8; ++k)
+                for (uint32_t v = 0; v < 16; ++v) t[k * 16 + v] = mat_vec(P, v << (4 * k));
+            P = mat_mul(P, P);
+        }
+    }
 }
 
 static int upload_params(const mtgp_params *h, const uint32_t *seeds, int n, void *d_params,

@@ -401,6 +401,7 @@ struct Seg {
     uint64_t c0 = 0;
     int D = 0;           // degree of the stream's polynomial
     int Dsize = 0;       // degree the workspace is sized for (>= D)
+    int group = 1;       // segments per work item (2, 4 or 8: a group; then c0 = 1)
     std::shared_ptr<StreamJump> sj;
 };
 
@@ -456,14 +457,54 @@ static uint64_t segment_length(uint64_t v) {
     return (v >> e) << e;
 }
 
+// Length of a group's segments for at least v outputs each: v rounded up to
+// m * 2^e, m in 16 .. 31 (at most 6% long), for the same reasons.
+static uint64_t group_length(uint64_t v) {
+    const int e = std::max(0, 63 - __builtin_clzll(v | 1) - 4);
+    return ((v + (1ull << e) - 1) >> e) << e;
+}
+
+// Segments of a request that would run together on one wave: as many as its
+// step width allows (group_members), fewer for short requests, 1 = no group.
+// A member pays a jump, about the time of 4,000 outputs at N = 101, so it
+// gets at least 16,384.
+static bool group_path(const ParamSet &ps, const Request &r, const mtgp_tuning &t) {
+    return has_groups(ps.N) && t.threads_per_stream == 64 && ps.lin[(size_t)r.stream] &&
+           ps.W[(size_t)r.stream] < (uint32_t)t.window_below_w;
+}
+
+static int group_size(const ParamSet &ps, const Request &r, const mtgp_tuning &t) {
+    if (!group_path(ps, r, t)) return 1;
+    const uint32_t W = ps.W[(size_t)r.stream];
+    int n = group_members(W);
+    // (a group of W > 32 is whole: its rows are compiled for all members)
+    while (n > 1 && r.count < (uint64_t)n * 16384u) n = W > 32 ? 1 : n / 2;
+    return n;
+}
+
 // Splits a request when it needs more than T dependent steps, for a stream
-// polynomial of degree D (D < 1: never).
+// polynomial of degree D (D < 1: never).  With `groups`, requests of narrow
+// streams are cut further, into whole groups.
 static void decide(const ParamSet &ps, const Request &r, int D, uint64_t T, const mtgp_tuning &t,
-                   Seg &g) {
+                   bool groups, Seg &g) {
     g.C = 1;
+    g.group = 1;
     g.D = g.Dsize = 0;
     if (!T || D < 1) return;
     const uint64_t so = step_outputs(ps, r.stream, t);
+    const int n = groups ? group_size(ps, r, t) : 1;
+    if (n > 1) {
+        const uint64_t items = std::max<uint64_t>(1, (r.count + so * T - 1) / (so * T));
+        const uint64_t lseg = group_length((r.count + items * n - 1) / (items * n));
+        if (lseg > (uint64_t)D + 1 && lseg < (1ull << 31) && r.count > lseg) {
+            g.C = (int)((r.count + lseg - 1) / lseg);
+            g.lseg = lseg;
+            g.c0 = 1;
+            g.group = n;
+            g.D = g.Dsize = D;
+            return;
+        }
+    }
     if ((r.count + so - 1) / so <= T) return;
     const uint64_t P = (uint64_t)D + 1;
     const uint64_t lseg = segment_length(T * so);
@@ -479,7 +520,8 @@ static void decide(const ParamSet &ps, const Request &r, int D, uint64_t T, cons
 static bool wants_split(const ParamSet &ps, const Request &r, uint64_t T, const mtgp_tuning &t) {
     if (!T) return false;
     const uint64_t so = step_outputs(ps, r.stream, t);
-    return (r.count + so - 1) / so > T && r.count > (uint64_t)ps.mexp + 128;
+    return ((r.count + so - 1) / so > T || group_size(ps, r, t) > 1) &&
+           r.count > (uint64_t)ps.mexp + 128;
 }
 
 constexpr int JUMP_BLOCKS_PER_CU = 3;
@@ -509,7 +551,7 @@ static Layout layout_for(const ParamSet &ps, const std::vector<Seg> &segs) {
         }
         ++nA;
         nB += ((size_t)g.C - 1 + 1) / 2 * (size_t)jump_passes(ps.N);  // at least two a block
-        nC += (size_t)g.C;
+        nC += ((size_t)g.C + (size_t)g.group - 1) / (size_t)g.group;
         poly_words += ((size_t)g.C - 1) * (((size_t)g.Dsize + 31) / 32);
         raw_words += ((size_t)ps.N + (size_t)g.Dsize + 1 + 63) / 64 * 64;
         js_words += (size_t)g.C * (size_t)ps.N;
@@ -760,14 +802,19 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
     }
     // plan, doubling the target until the workspace fits
     Layout L;
+    bool groups = true;  // given up first where the workspace is small
     while (true) {
         for (size_t i = 0; i < reqs.size(); ++i) {
             const int D = (sjs[i] && sjs[i]->status == 1) ? sjs[i]->D : 0;
-            decide(*ps, reqs[i], D, T, t, segs[i]);
+            decide(*ps, reqs[i], D, T, t, groups, segs[i]);
             segs[i].sj = segs[i].C > 1 ? sjs[i] : nullptr;
         }
         L = layout_for(*ps, segs);
         if (L.total <= ws_bytes || !T) break;
+        if (groups) {
+            groups = false;
+            continue;
+        }
         T *= 2;
         if (T > (1ull << 40)) T = 0;
     }
@@ -825,9 +872,33 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
             b.out = (uint64_t)(uintptr_t)((char *)r.d_out + out_off * 4);
             return b;
         };
+        // A wave of a stream with 32 < W < 64 is a group of one: no scan, and
+        // the outputs leave from the registers of the chain.
+        const bool alone = group_path(*ps, r, t) && group_log(ps->W[(size_t)r.stream]) == 0 &&
+                           r.count < (1ull << 31);
+        auto group_item = [&](int k, int n, uint64_t states, uint64_t lseg, uint64_t rec,
+                              uint64_t prefix) {
+            GroupItem gi;
+            gi.stream = (uint32_t)r.stream;
+            gi.mode = mode | MODE_GROUP;
+            gi.count = r.count;
+            gi.out = (uint64_t)(uintptr_t)r.d_out;
+            gi.states = states;
+            gi.state_out = (uint64_t)(uintptr_t)row;
+            gi.lseg = lseg;
+            gi.first = (uint32_t)k;
+            gi.n = (uint32_t)n;
+            gi.rec = rec;
+            gi.flag = 0;
+            gi.prefix = prefix;
+            BatchItem b;
+            std::memcpy(&b, &gi, sizeof b);
+            return b;
+        };
         if (g.C <= 1) {
             BatchItem b = base_item(r.count, 0);
             b.state_in = b.state_out = (uint64_t)(uintptr_t)row;
+            if (alone) b = group_item(0, 1, (uint64_t)(uintptr_t)row, r.count, 0, 0);
             b.flag = r.flag;
             C.push_back(CItem{(r.count + so - 1) / so, b, false});
             continue;
@@ -892,7 +963,13 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
         }
         // C: segments; every one but the last checks its end state against
         // the next one's jumped start
-        for (int k = 0; k < g.C; ++k) {
+        const bool grouped = g.group > 1 || (alone && g.c0 == 1);
+        for (int k = 0; grouped && k < g.C; k += g.group) {
+            const int n = std::min(g.group, g.C - k);
+            C.push_back(CItem{((uint64_t)n * g.lseg + so - 1) / so,
+                              group_item(k, n, (uint64_t)(uintptr_t)js, g.lseg, rec_dev, P), true});
+        }
+        for (int k = 0; !grouped && k < g.C; ++k) {
             const uint64_t c = k == 0 ? 0 : g.c0 + (uint64_t)k - 1;
             const uint64_t start = k == 0 ? P : c * g.lseg;
             const uint64_t end = std::min<uint64_t>(r.count, k == 0 ? g.c0 * g.lseg
@@ -1236,12 +1313,12 @@ int mtgp_batch_workspace_query(const void *d_params, const mtgp_work *h_items, i
             const StreamJump *sj = ps->jumps[(size_t)k].get();
             segs[i].req = (int)i;
             if (sj && sj->status == 1 && !ps->dirty[(size_t)k]) {
-                decide(*ps, reqs[i], sj->D, T, t, segs[i]);
+                decide(*ps, reqs[i], sj->D, T, t, true, segs[i]);
             } else if (!sj || ps->dirty[(size_t)k]) {
                 // the polynomial will be built from the stream's state at
                 // generation time: size for the most segments (D = 1) and
                 // the largest degree (mexp)
-                decide(*ps, reqs[i], 1, T, t, segs[i]);
+                decide(*ps, reqs[i], 1, T, t, true, segs[i]);
                 if (segs[i].C > 1) segs[i].Dsize = (int)ps->mexp;
             }
         }

@@ -28,11 +28,25 @@ enum : uint32_t {
     P_WIN_Q = 66,        // lanes per residue class (64 / W)
     P_WIN_ROUNDS = 67,   // cross-lane scan rounds, ceil(log2 q)
     P_WIN_MAT = 128,     // nibble tables of M^(E*2^r): [round][nibble][16]
+    P_GRP_MAT = 768,     // groups with several lanes per class: M^(8*2^r), r < 2
     P_WORDS = 1024,      // 4 KB per stream
 };
 constexpr int WIN_EMAX = 8;
 constexpr int WIN_MAXROUNDS = 5;
 constexpr int WIN_MAT_WORDS = 128;   // 8 nibbles x 16 entries
+
+// Groups: several segments of one narrow stream run together on one wave,
+// where a whole wave's window of a short state would be cut into tiny chunks
+// per residue class.  W <= 32: 2^group_log(W) segments, each on
+// 64 >> group_log(W) lanes; W > 32: every lane takes its class of each of
+// GROUP_ROWS segments.  Only for N <= 128 (several states fit a wave's LDS)
+// and linear recursion tables.
+constexpr bool has_groups(int N) { return N <= 128; }
+constexpr int group_log(uint32_t W) { return W <= 8 ? 3 : W <= 16 ? 2 : W <= 32 ? 1 : 0; }
+constexpr int GROUP_ROWS = 4;
+constexpr int group_members(uint32_t W) { return W <= 32 ? 1 << group_log(W) : GROUP_ROWS; }
+constexpr int GROUP_E = 8;           // most elements per lane and window
+constexpr int GROUP_ROUNDS = 2;      // scan rounds (W = 2: four lanes per class)
 
 // BatchItem.mode bits
 enum : uint32_t {
@@ -43,6 +57,7 @@ enum : uint32_t {
     MODE_FIXUP = 8u,   // request check (last launch of a batch): regenerate
                        // the request from its record if a segment failed,
                        // then raise `flag`
+    MODE_GROUP = 16u,  // segments of a split request, or a whole one (GroupItem)
 };
 
 // Request record (64 bytes) of a request split by jump-ahead: its segments
@@ -78,6 +93,26 @@ struct BatchItem {
     uint64_t reserved;
 };
 static_assert(sizeof(BatchItem) == 80, "BatchItem layout");
+
+// A BatchItem with MODE_GROUP: segments first .. first + n - 1 of a split
+// request (a whole request: lseg = count, prefix = 0).  Segment k covers outputs [start, end) of the request with
+// start = prefix (k = 0) or k * lseg and end = min(count, (k+1) * lseg); its
+// start state is states + k * N words, and its end state must equal segment
+// k+1's start state, or goes to state_out when it ends the request.
+struct GroupItem {
+    uint32_t stream;
+    uint32_t mode;
+    uint64_t count;      // of the whole request
+    uint64_t out;        // of the whole request
+    uint64_t states;
+    uint64_t state_out;
+    uint64_t lseg;
+    uint32_t first, n;
+    uint64_t rec;
+    uint64_t flag;       // 0: the request's check item raises it
+    uint64_t prefix;     // outputs the prefix item makes
+};
+static_assert(sizeof(GroupItem) == sizeof(BatchItem), "GroupItem layout");
 
 // Batch workspace header (256 bytes, never part of an uploaded plan):
 //   word 0, 1   claim counters of the prefix and segment launches

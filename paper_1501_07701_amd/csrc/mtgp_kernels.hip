@@ -113,7 +113,14 @@ struct Core {
     static constexpr int WNMAX = (N - 1) < 64 * WIN_EMAX ? (N - 1) : 64 * WIN_EMAX;
     static constexpr int WTAIL = 32 + 64 + WIN_MAXROUNDS * WIN_MAT_WORDS;
     static constexpr int WLDS = (N + WNMAX + 63) / 64 * 64 + WTAIL;
-    static constexpr int LDS_WORDS = (BUF + 32) > WLDS ? (BUF + 32) : WLDS;
+    // Group path: the members' buffers (eight of a state and two windows, or
+    // fewer longer ones), the tables and the scan matrices.
+    static constexpr bool GROUPS = TPS == 64 && has_groups(N);
+    static constexpr int GTAIL = 32 + GROUP_ROUNDS * WIN_MAT_WORDS;
+    static constexpr int GLDS = GROUPS ? 8 * (N + 2 * 64) + GTAIL : 0;
+    static constexpr int WIDE_LDS = (BUF + 32) > WLDS ? (BUF + 32) : WLDS;
+    static constexpr int LDS_WORDS = WIDE_LDS > GLDS ? WIDE_LDS : GLDS;
+    static constexpr int GBUF = LDS_WORDS - GTAIL;
     static constexpr int WBUF = LDS_WORDS - WTAIL;
     static_assert(WBUF >= N + WNMAX, "window buffer too small");
 
@@ -549,6 +556,314 @@ struct Core {
         }
     }
 
+    // A group of segments of one narrow stream with a linear recursion table:
+    // member m on lanes [m GL, (m+1) GL), GL = 64 >> lg, each in its own part
+    // of the LDS block, all in step.  A window of wn <= N-1 words per member
+    // is the affine chain of steps_window_e over q = GL / W lanes per residue
+    // class, E elements each; q is 1 but for W <= 4, so there is mostly no
+    // scan and no second pass, and the outputs leave from the registers of
+    // the chain (pieces of W words; L2 joins them to lines).  Members shorter
+    // than the longest (the first segment, the last) stop storing at their
+    // end, where their end state is checked or kept.  4000 mexp-3217 streams
+    // of 2^18 outputs, segments alone: W = 2 2.2 TB/s (one segment per wave,
+    // window scan: 0.9), W = 8 3.4 (1.2), W = 16 3.9 (1.5), W = 32 4.1 (1.9).
+    template <bool F32, int E, bool SCAN>
+    static __device__ __forceinline__ void steps_group(const Step &p, const GroupItem &item,
+                                                       uint32_t *__restrict__ buf, uint32_t lg,
+                                                       uint32_t q, uint32_t wn, uint32_t lane,
+                                                       uint32_t *fail) {
+        const uint32_t *tbl = buf + GBUF;
+        const uint32_t *mats = tbl + 32;
+        const uint32_t GL = 64u >> lg, seg = (uint32_t)GBUF >> lg;
+        const uint32_t m = lane >> (6u - lg), gl = lane & (GL - 1u);
+        const uint32_t W = p.W;
+        const uint32_t r = SCAN ? gl / q : gl, sub = SCAN ? gl - r * q : 0u;
+        const uint32_t off0 = r + W * (sub * (uint32_t)E);
+        const bool ok = r < W;
+        uint32_t *b = buf + m * seg;
+        // this lane's member: its outputs and start state
+        const uint32_t k = item.first + m;
+        const uint64_t start = k == 0 ? item.prefix : (uint64_t)k * item.lseg;
+        const uint64_t stop = (uint64_t)(k + 1) * item.lseg;
+        const uint64_t end = stop < item.count ? stop : item.count;
+        const uint32_t cnt = m < item.n ? (uint32_t)(end - start) : 0u;
+        uint32_t most = cnt;
+#pragma unroll
+        for (int d = 8; d < 64; d <<= 1) {
+            const uint32_t o = (uint32_t)__shfl_xor((int)most, d, 64);
+            most = o > most ? o : most;
+        }
+        most = __builtin_amdgcn_readfirstlane(most);
+        const uint32_t *st = reinterpret_cast<const uint32_t *>(item.states) + (uint64_t)k * N;
+        if (cnt)
+            for (uint32_t i = gl; i < (uint32_t)N; i += GL) b[i] = st[i];
+        gptr<uint32_t> out = (gptr<uint32_t>)(reinterpret_cast<uint32_t *>(item.out)) + start;
+        group_sync<TPS>();
+        uint32_t h = N;
+        for (uint32_t done = 0; done < most; done += wn, h += wn) {
+            if (h + wn > seg) {  // the newest N words to the front, in order
+                const uint32_t *src = b + (h - N);
+                for (uint32_t i0 = 0; i0 < (uint32_t)N; i0 += 8 * GL) {
+                    uint32_t t[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const uint32_t i = i0 + gl + GL * j;
+                        t[j] = src[i < (uint32_t)N ? i : 0u];
+                    }
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) {
+                        const uint32_t i = i0 + gl + GL * j;
+                        if (i < (uint32_t)N) b[i] = t[j];
+                    }
+                }
+                group_sync<TPS>();
+                h = N;
+            }
+            uint32_t *w = b + h + off0;
+            uint32_t X[E], v[E];
+            if (ok) {
+#pragma unroll
+                for (int j = 0; j < E; ++j) {
+                    // past the window's end only with a scan's last chunks
+                    const uint32_t *s = !SCAN || off0 + W * j < wn ? w + W * j - N : b + h - N;
+                    const uint32_t x0 = (s[0] & p.mask) ^ s[1];
+                    X[j] = x0 ^ (x0 << p.sh1);
+                }
+                uint32_t c = sub == 0 ? b[h + r - W] : 0u;
+                if constexpr (SCAN) {
+                    uint32_t u = c;
+#pragma unroll
+                    for (int j = 0; j < E; ++j) u = rec<false>(p, tbl, X[j] ^ (u >> p.sh2));
+#pragma unroll
+                    for (int i = 0; i < GROUP_ROUNDS; ++i) {
+                        const uint32_t d = 1u << i;
+                        const uint32_t o = (uint32_t)__shfl((int)u, (int)(sub >= d ? lane - d : lane), 64);
+                        const uint32_t y = mat_apply(mats + i * WIN_MAT_WORDS, o);
+                        if (sub >= d) u ^= y;
+                    }
+                    const uint32_t in = (uint32_t)__shfl((int)u, (int)(sub ? lane - 1 : lane), 64);
+                    if (sub) c = in;
+                }
+#pragma unroll
+                for (int j = 0; j < E; ++j) {
+                    v[j] = c = rec<false>(p, tbl, X[j] ^ (c >> p.sh2));
+                    if (!SCAN || off0 + W * j < wn) w[W * j] = c;
+                }
+            }
+            group_sync<TPS>();
+            if constexpr (SCAN) {
+                for (uint32_t i = gl; i < wn; i += GL)
+                    if (done + i < cnt)
+                        out[done + i] = temper<F32>(tbl, b[h + i], b[h + i - W - 1]);
+            } else if (ok) {
+                uint32_t t[E];
+#pragma unroll
+                for (int j = 0; j < E; ++j) t[j] = *(w + W * j - W - 1);
+#pragma unroll
+                for (int j = 0; j < E; ++j) t[j] = temper<F32>(tbl, v[j], t[j]);
+                gptr<uint32_t> o = out + (done + off0);
+                if (done + wn <= cnt) {
+#pragma unroll
+                    for (int j = 0; j < E; ++j) o[W * j] = t[j];
+                } else {
+#pragma unroll
+                    for (int j = 0; j < E; ++j)
+                        if (done + off0 + W * j < cnt) o[W * j] = t[j];
+                }
+            }
+            if (cnt > done && cnt <= done + wn) {  // this member ends here
+                const uint32_t *e = b + h + (cnt - done) - N;
+                if (end == item.count) {
+                    uint32_t *row = reinterpret_cast<uint32_t *>(item.state_out);
+                    for (uint32_t i = gl; i < (uint32_t)N; i += GL) row[i] = e[i];
+                } else {
+                    const uint32_t *next = st + N;
+                    uint32_t bad = 0;
+                    for (uint32_t i = gl; i < (uint32_t)N; i += GL)
+                        bad |= e[i] != next[i] ? 1u : 0u;
+                    if (bad) atomicOr(fail, 1u);
+                }
+            }
+            group_sync<TPS>();
+        }
+    }
+
+    // A group of a stream with 32 < W < 64: lane l < W takes residue class l of
+    // each of R members, so that R chains are in flight per lane (a single
+    // segment's window of at most three elements leaves the wave waiting).
+    // The same streams with W = 33 2.8 TB/s (2.0), W = 50 3.6 (2.5), W = 63
+    // 3.8 (2.6).
+    template <bool F32, int E, int R>
+    static __device__ __forceinline__ void steps_rows(const Step &p, const GroupItem &item,
+                                                      uint32_t *__restrict__ buf, uint32_t lane,
+                                                      uint32_t *fail) {
+        constexpr uint32_t SEG = (uint32_t)GBUF / R;
+        static_assert(!GROUPS || SEG >= 2 * N, "a row holds a state and a window");
+        const uint32_t *tbl = buf + GBUF;
+        const uint32_t W = p.W, wn = W * E;
+        const bool ok = lane < W;
+        uint32_t cnt[R], most = 0;
+        gptr<uint32_t> out[R];
+#pragma unroll
+        for (int m = 0; m < R; ++m) {
+            const uint32_t k = item.first + m;
+            const uint64_t start = k == 0 ? item.prefix : (uint64_t)k * item.lseg;
+            const uint64_t stop = (uint64_t)(k + 1) * item.lseg;
+            const uint64_t end = stop < item.count ? stop : item.count;
+            cnt[m] = (uint32_t)m < item.n ? (uint32_t)(end - start) : 0u;
+            most = cnt[m] > most ? cnt[m] : most;
+            out[m] = (gptr<uint32_t>)(reinterpret_cast<uint32_t *>(item.out)) + start;
+            const uint32_t *st = reinterpret_cast<const uint32_t *>(item.states) + (uint64_t)k * N;
+            if (cnt[m])
+                for (uint32_t i = lane; i < (uint32_t)N; i += 64) buf[m * SEG + i] = st[i];
+        }
+        group_sync<TPS>();
+        uint32_t h = N;
+        for (uint32_t done = 0; done < most; done += wn, h += wn) {
+            if (h + wn > SEG) {  // the newest N words to the front, in order
+                constexpr int C = (N + 63) / 64;
+                uint32_t t[R][C];
+#pragma unroll
+                for (int m = 0; m < R; ++m)
+#pragma unroll
+                    for (int j = 0; j < C; ++j) {
+                        const uint32_t i = lane + 64u * j;
+                        t[m][j] = buf[m * SEG + h - N + (i < (uint32_t)N ? i : 0u)];
+                    }
+#pragma unroll
+                for (int m = 0; m < R; ++m)
+#pragma unroll
+                    for (int j = 0; j < C; ++j) {
+                        const uint32_t i = lane + 64u * j;
+                        if (i < (uint32_t)N) buf[m * SEG + i] = t[m][j];
+                    }
+                group_sync<TPS>();
+                h = N;
+            }
+            uint32_t *w = buf + h + lane;
+            uint32_t X[R][E], v[R][E];
+            if (ok) {
+                uint32_t c[R];
+#pragma unroll
+                for (int m = 0; m < R; ++m) {
+                    c[m] = *(w + m * SEG - W);
+#pragma unroll
+                    for (int j = 0; j < E; ++j) {
+                        const uint32_t *s = w + m * SEG + W * j - N;
+                        const uint32_t x0 = (s[0] & p.mask) ^ s[1];
+                        X[m][j] = x0 ^ (x0 << p.sh1);
+                    }
+                }
+#pragma unroll
+                for (int j = 0; j < E; ++j)
+#pragma unroll
+                    for (int m = 0; m < R; ++m) {
+                        v[m][j] = c[m] = rec<false>(p, tbl, X[m][j] ^ (c[m] >> p.sh2));
+                        w[m * SEG + W * j] = c[m];
+                    }
+            }
+            group_sync<TPS>();
+            if (ok) {
+                uint32_t t[R][E];
+#pragma unroll
+                for (int m = 0; m < R; ++m)
+#pragma unroll
+                    for (int j = 0; j < E; ++j) t[m][j] = *(w + m * SEG + W * j - W - 1);
+#pragma unroll
+                for (int m = 0; m < R; ++m)
+#pragma unroll
+                    for (int j = 0; j < E; ++j) t[m][j] = temper<F32>(tbl, v[m][j], t[m][j]);
+#pragma unroll
+                for (int m = 0; m < R; ++m) {
+                    gptr<uint32_t> o = out[m] + done + lane;
+                    if (done + wn <= cnt[m]) {
+#pragma unroll
+                        for (int j = 0; j < E; ++j) o[W * j] = t[m][j];
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < E; ++j)
+                            if (done + lane + W * j < cnt[m]) o[W * j] = t[m][j];
+                    }
+                }
+            }
+#pragma unroll
+            for (int m = 0; m < R; ++m)
+                if (cnt[m] > done && cnt[m] <= done + wn) {  // this member ends here
+                    const uint32_t k = item.first + m;
+                    const uint32_t *e = buf + m * SEG + h + (cnt[m] - done) - N;
+                    if ((uint64_t)(k + 1) * item.lseg >= item.count) {
+                        uint32_t *row = reinterpret_cast<uint32_t *>(item.state_out);
+                        for (uint32_t i = lane; i < (uint32_t)N; i += 64) row[i] = e[i];
+                    } else {
+                        const uint32_t *next = reinterpret_cast<const uint32_t *>(item.states) +
+                                               (uint64_t)(k + 1) * N;
+                        uint32_t bad = 0;
+                        for (uint32_t i = lane; i < (uint32_t)N; i += 64)
+                            bad |= e[i] != next[i] ? 1u : 0u;
+                        if (bad) atomicOr(fail, 1u);
+                    }
+                }
+            group_sync<TPS>();
+        }
+    }
+
+    template <bool F32>
+    static __device__ __forceinline__ void run_group(const uint32_t *__restrict__ prm,
+                                                     const GroupItem &item,
+                                                     uint32_t *__restrict__ buf, uint32_t lane) {
+        Step p = load_step(prm);
+        const uint32_t lg = (uint32_t)group_log(p.W), GL = 64u >> lg, q = GL / p.W;
+        uint32_t *tbl = buf + GBUF;
+        group_sync<TPS>();  // the previous user of this buffer is done with it
+        if (lane < 16) {
+            tbl[lane] = prm[P_REC + lane];
+            tbl[16 + lane] = prm[(F32 ? P_FLT : P_TMP) + lane];
+        }
+        uint32_t *fail = &reinterpret_cast<ReqRec *>(item.rec)->failed;
+        if (p.W > 32u) {
+            group_sync<TPS>();
+#define MTGP_GR(E)                                                        \
+    case E:                                                               \
+        if (item.n > 1u) steps_rows<F32, E, GROUP_ROWS>(p, item, buf, lane, fail); \
+        else steps_rows<F32, E, 1>(p, item, buf, lane, fail);             \
+        break;
+            switch ((N - 1) / p.W) {  // E W < N, W > 32, N <= 128
+                MTGP_GR(1) MTGP_GR(2) MTGP_GR(3)
+                default: break;
+            }
+#undef MTGP_GR
+            return;
+        }
+        if (q > 1u) {
+            for (uint32_t i = lane; i < (uint32_t)(GROUP_ROUNDS * WIN_MAT_WORDS); i += 64)
+                tbl[32 + i] = prm[P_GRP_MAT + i];
+            // W q E words, E = 8 (W <= 4, q = 8 / W)
+            steps_group<F32, GROUP_E, true>(p, item, buf, lg, q, p.W * q * GROUP_E, lane, fail);
+            return;
+        }
+        switch ((N - 1) / p.W) {  // whole windows of E W words
+#define MTGP_GE(E) \
+    case E: steps_group<F32, E, false>(p, item, buf, lg, 1u, p.W * E, lane, fail); break;
+            MTGP_GE(1) MTGP_GE(2) MTGP_GE(3) MTGP_GE(4) MTGP_GE(5) MTGP_GE(6) MTGP_GE(7)
+#undef MTGP_GE
+            default: steps_group<F32, 8, false>(p, item, buf, lg, 1u, p.W * 8, lane, fail); break;
+        }
+    }
+
+    static __device__ __forceinline__ Step load_step(const uint32_t *__restrict__ prm) {
+        Step p;
+        p.pos = prm[P_POS];
+        p.sh1 = prm[P_SH1];
+        p.sh2 = prm[P_SH2];
+        p.mask = prm[P_MASK];
+        p.W = N - p.pos;
+        p.rb0 = prm[P_RB + 0];
+        p.rb1 = prm[P_RB + 1];
+        p.rb2 = prm[P_RB + 2];
+        p.rb3 = prm[P_RB + 3];
+        return p;
+    }
+
     // Advance one stream by item.count outputs.  A MODE_VERIFY item that
     // ends in a state other than item.verify sets *fail.  RAW: the
     // MODE_RAW word dump is compiled in (prefix kernels only); LAT: narrow
@@ -561,16 +876,7 @@ struct Core {
         // a stream takes the window path when the host gave it window data
         const bool win = TPS == 64 && prm[P_WIN_E] != 0u && prm[P_W] < win_below;
         uint32_t *__restrict__ tbl = buf + (win ? WBUF : BUF);
-        Step p;
-        p.pos = prm[P_POS];
-        p.sh1 = prm[P_SH1];
-        p.sh2 = prm[P_SH2];
-        p.mask = prm[P_MASK];
-        p.W = N - p.pos;
-        p.rb0 = prm[P_RB + 0];
-        p.rb1 = prm[P_RB + 1];
-        p.rb2 = prm[P_RB + 2];
-        p.rb3 = prm[P_RB + 3];
+        const Step p = load_step(prm);
         const uint32_t lin = prm[P_LIN];
         const uint64_t count = item.count;
         const uint32_t *st_in = reinterpret_cast<const uint32_t *>(item.state_in);
@@ -681,7 +987,14 @@ __device__ __forceinline__ void gen_body(const uint32_t *__restrict__ params,
             item.state_in = item.state_out = (uint64_t)(uintptr_t)row;
             item.raw = item.verify = item.rec = item.flag = 0;
         }
-        if (item.count > 0) {
+        if (C::GROUPS && !RAW && !LAT && (item.mode & MODE_GROUP)) {
+            if constexpr (C::GROUPS && !RAW && !LAT) {
+                const GroupItem g = *reinterpret_cast<const GroupItem *>(items + it);
+                const uint32_t *prm = params + (uint64_t)g.stream * P_WORDS;
+                if (g.mode & MODE_F32) C::template run_group<true>(prm, g, buf, lane);
+                else C::template run_group<false>(prm, g, buf, lane);
+            }
+        } else if (item.count > 0) {
             const uint32_t *prm = params + (uint64_t)item.stream * P_WORDS;
             uint32_t *fail = (item.mode & MODE_VERIFY)
                                  ? &reinterpret_cast<ReqRec *>(item.rec)->failed
