@@ -117,26 +117,43 @@ Poly shl(const Poly &a, int n) {
     return r;
 }
 
-// r ^= p * x^sh, with p of n words
+// r ^= p * x^sh, with p of pn words; bits past r's rn words are dropped.
 static void xor_shifted(uint64_t *r, size_t rn, const uint64_t *p, size_t pn, int sh) {
     const size_t q = (size_t)sh >> 6;
     const int s = sh & 63;
-    for (size_t i = 0; i < pn; ++i) {
-        if (i + q < rn) r[i + q] ^= p[i] << s;
-        if (s && i + q + 1 < rn) r[i + q + 1] ^= p[i] >> (64 - s);
+    if (q >= rn) return;
+    r += q;
+    rn -= q;
+    if (s == 0) {
+        const size_t n = pn < rn ? pn : rn;
+        for (size_t i = 0; i < n; ++i) r[i] ^= p[i];
+        return;
     }
+    if (pn == 0) return;
+    r[0] ^= p[0] << s;
+    const size_t n = pn < rn ? pn : rn;
+    for (size_t i = 1; i < n; ++i) r[i] ^= (p[i] << s) | (p[i - 1] >> (64 - s));
+    if (pn < rn) r[pn] ^= p[pn - 1] >> (64 - s);
+}
+
+// degree of the lowest `words` words of a
+static int degree_within(const Poly &a, size_t words) {
+    for (size_t w = words; w-- > 0;)
+        if (a[w]) return (int)(w * 64 + 63 - __builtin_clzll(a[w]));
+    return -1;
 }
 
 static Poly divmod(const Poly &a, const Poly &p, Poly *quot) {
     const int dp = degree(p);
+    const size_t pw = (size_t)dp / 64 + 1;
     Poly r = a;
     int dr = degree(r);
     if (quot) quot->assign(dr >= dp ? (size_t)((dr - dp) / 64 + 1) : 0, 0);
     while (dr >= dp) {
         const int sh = dr - dp;
-        xor_shifted(r.data(), r.size(), p.data(), p.size(), sh);
+        xor_shifted(r.data(), r.size(), p.data(), pw, sh);
         if (quot) (*quot)[(size_t)sh >> 6] |= 1ull << (sh & 63);
-        dr = degree(r);
+        dr = degree_within(r, (size_t)dr / 64 + 1);  // it only falls
     }
     trim(r);
     if (quot) trim(*quot);
@@ -232,36 +249,43 @@ int berlekamp_massey(const uint8_t *bits, int n, Poly *annihilator) {
     Poly C(nw, 0), B(nw, 0), T;
     C[0] = B[0] = 1;
     // window[i] = s_{k-i}: kept as a reversed packed copy of the prefix
-    Poly rev((size_t)n / 64 + 2, 0);  // rev bit (n-1-t) = s_t
+    Poly rev((size_t)n / 64 + 3, 0);  // rev bit (n-1-t) = s_t
     for (int t = 0; t < n; ++t)
         if (bits[t] & 1) rev[(size_t)(n - 1 - t) >> 6] |= 1ull << ((n - 1 - t) & 63);
     int L = 0, m = 1;
+    size_t bw = 1;  // words of B that may be nonzero (its degree is at most its L)
     for (int k = 0; k < n; ++k) {
         // d = sum_{i=0..L} C_i s_{k-i};  s_{k-i} = rev bit (n-1-k+i)
+        // (rev has a word past any that is read)
         const int base = n - 1 - k;
-        uint64_t acc = 0;
         const int words = L / 64 + 1;
-        for (int w = 0; w < words; ++w) {
-            const int pos = base + 64 * w;
-            const size_t q = (size_t)pos >> 6;
-            const int s = pos & 63;
-            uint64_t win = rev[q] >> s;
-            if (s && q + 1 < rev.size()) win |= rev[q + 1] << (64 - s);
-            if (w == words - 1 && ((L + 1) & 63)) win &= (1ull << ((L + 1) & 63)) - 1;
-            acc ^= C[w] & win;
+        const uint64_t *rv = rev.data() + ((size_t)base >> 6);
+        const int s = base & 63;
+        uint64_t acc = 0, last;
+        if (s == 0) {
+            for (int w = 0; w < words - 1; ++w) acc ^= C[w] & rv[w];
+            last = rv[words - 1];
+        } else {
+            for (int w = 0; w < words - 1; ++w)
+                acc ^= C[w] & ((rv[w] >> s) | (rv[w + 1] << (64 - s)));
+            last = (rv[words - 1] >> s) | (rv[words] << (64 - s));
         }
+        if ((L + 1) & 63) last &= (1ull << ((L + 1) & 63)) - 1;
+        acc ^= C[words - 1] & last;
         if (!__builtin_parityll(acc)) {
             ++m;
             continue;
         }
         if (2 * L <= k) {
-            T = C;
-            xor_shifted(C.data(), C.size(), B.data(), B.size(), m);
+            const size_t cw = (size_t)L / 64 + 1;
+            T.assign(C.begin(), C.begin() + (ptrdiff_t)cw);
+            xor_shifted(C.data(), C.size(), B.data(), bw, m);
             L = k + 1 - L;
-            B = std::move(T);
+            std::swap(B, T);
+            bw = cw;
             m = 1;
         } else {
-            xor_shifted(C.data(), C.size(), B.data(), B.size(), m);
+            xor_shifted(C.data(), C.size(), B.data(), bw, m);
             ++m;
         }
     }
