@@ -233,6 +233,13 @@ hipError_t launch_workgroup(const uint32_t *params, uint32_t *states, uint32_t s
                             uint32_t threads, uint32_t n_words, hipStream_t s);
 hipError_t launch_screen(const uint32_t *out, uint32_t n_streams, uint64_t count, uint32_t lo,
                          uint32_t hi, uint32_t bins, uint64_t *counts, hipStream_t s);
+// Piece of a result copy: `bytes` (at most COPY_PIECE) from src to dst.
+constexpr uint64_t COPY_PIECE = 64 << 10;
+struct CopyPiece {
+    uint64_t src, dst, bytes;
+};
+// Copies n pieces; the list may lie in host-mapped memory.
+hipError_t launch_copy(const CopyPiece *pieces, uint32_t n, hipStream_t s);
 hipError_t launch_fill(uint32_t *out, uint64_t n_words, uint32_t value, int num_cus,
                        hipStream_t s);
 

@@ -1575,6 +1575,27 @@ fill_kernel(u32x4 *__restrict__ out, uint64_t n_vec, uint32_t *__restrict__ tail
     if (blockIdx.x == 0 && threadIdx.x < n_tail) tail[threadIdx.x] = value;
 }
 
+// Copies a list of pieces, one workgroup each, by the widest unit that source,
+// destination and size allow.  Results that come back together leave in one
+// launch: a copy command each costs the caller about 5 us, more than the
+// bytes of a short result (1000 requests, 0.5 GB: 3.9 ms against 6.0).
+template <typename T>
+__device__ __forceinline__ void copy_units(const CopyPiece &c) {
+    gptr<const T> src = (gptr<const T>)(reinterpret_cast<const T *>(c.src));
+    gptr<T> dst = (gptr<T>)(reinterpret_cast<T *>(c.dst));
+    const uint32_t n = (uint32_t)(c.bytes / sizeof(T));
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) dst[i] = src[i];
+}
+
+__global__ void __launch_bounds__(256)
+copy_kernel(const CopyPiece *__restrict__ pieces) {
+    const CopyPiece c = pieces[blockIdx.x];
+    const uint64_t all = c.src | c.dst | c.bytes;
+    if ((all & 15u) == 0) copy_units<u32x4>(c);
+    else if ((all & 3u) == 0) copy_units<uint32_t>(c);
+    else copy_units<uint8_t>(c);
+}
+
 // ------------------------------------------------------------- dispatch --
 
 typedef void (*GenFn)(const uint32_t *, const BatchItem *, uint32_t, uint32_t *, uint32_t,
@@ -2137,6 +2158,13 @@ hipError_t launch_screen(const uint32_t *out, uint32_t n_streams, uint64_t count
         launch_screen_n<16>(out, n_streams, count, lo, hi, bins, counts, s);
     else
         launch_screen_n<4>(out, n_streams, count, lo, hi, bins, counts, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy(const CopyPiece *pieces, uint32_t n, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    (void)hipGetLastError();  // report this launch only
+    hipLaunchKernelGGL(copy_kernel, dim3(n), dim3(256), 0, s, pieces);
     return hipGetLastError();
 }
 

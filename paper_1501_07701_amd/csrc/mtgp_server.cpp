@@ -65,6 +65,7 @@ class HipBackend final : public SchedBackend {
             if (sl.hs) (void)hipStreamDestroy(sl.hs);
         }
         if (copy_stream_) (void)hipStreamDestroy(copy_stream_);
+        if (copy_list_) (void)hipHostFree(copy_list_);
     }
 
     void thread_start() override { (void)hipSetDevice(device); }
@@ -123,13 +124,47 @@ class HipBackend final : public SchedBackend {
                 return hip_fail(e, "hipStreamCreate(result copies)");
             }
         }
+        // one launch for all results that lie in this GPU's memory; others
+        // (another GPU's, mapped host memory) by a copy command each
         int rc = MTGP_OK;
+        std::vector<CopyPiece> pieces;
         for (const Copy &c : copies) {
+            hipPointerAttribute_t at{};
+            const bool here = hipPointerGetAttributes(&at, c.dst) == hipSuccess &&
+                              at.type == hipMemoryTypeDevice && at.device == device;
+            if (here) {
+                const uint64_t src = (uint64_t)(uintptr_t)(d_pool + c.off),
+                               dst = (uint64_t)(uintptr_t)c.dst;
+                for (uint64_t o = 0; o < c.bytes; o += COPY_PIECE)
+                    pieces.push_back(CopyPiece{src + o, dst + o,
+                                               std::min<uint64_t>(COPY_PIECE, c.bytes - o)});
+                continue;
+            }
+            (void)hipGetLastError();  // the attribute query's
             hipError_t e = hipMemcpyAsync(c.dst, d_pool + c.off, c.bytes, hipMemcpyDeviceToDevice,
                                           copy_stream_);
             if (e != hipSuccess && rc == MTGP_OK) rc = hip_fail(e, "hipMemcpyAsync(kept result)");
         }
-        hipError_t e = hipStreamSynchronize(copy_stream_);
+        hipError_t e = hipSuccess;
+        if (!pieces.empty()) {
+            if (pieces.size() > copy_cap_) {  // (no copy is running: each call waits for its own)
+                if (copy_list_) (void)hipHostFree(copy_list_);
+                copy_list_ = nullptr;
+                copy_cap_ = std::max<size_t>(pieces.size() * 2, 1024);
+                e = hipHostMalloc((void **)&copy_list_, copy_cap_ * sizeof(CopyPiece),
+                                  hipHostMallocMapped | hipHostMallocCoherent);
+                if (e != hipSuccess) {
+                    copy_list_ = nullptr;
+                    copy_cap_ = 0;
+                }
+            }
+            if (e == hipSuccess) {
+                std::memcpy(copy_list_, pieces.data(), pieces.size() * sizeof(CopyPiece));
+                e = launch_copy(copy_list_, (uint32_t)pieces.size(), copy_stream_);
+            }
+            if (e != hipSuccess && rc == MTGP_OK) rc = hip_fail(e, "kept results' copy");
+        }
+        e = hipStreamSynchronize(copy_stream_);
         if (e != hipSuccess && rc == MTGP_OK) rc = hip_fail(e, "hipStreamSynchronize(kept)");
         return rc;
     }
@@ -137,6 +172,8 @@ class HipBackend final : public SchedBackend {
    private:
     std::mutex copy_mu_;
     hipStream_t copy_stream_ = nullptr;
+    CopyPiece *copy_list_ = nullptr;  // pinned, host-mapped
+    size_t copy_cap_ = 0;
 };
 
 }  // namespace
