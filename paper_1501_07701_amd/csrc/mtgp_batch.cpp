@@ -124,18 +124,14 @@ static void parallel_for(int n, F f) {
     for (auto &x : th) x.join();
 }
 
-// Cost model: outputs a stream yields per dependent step of the wide path
-// (one LDS round trip).  Narrow streams with a linear rec_tbl run the
-// windowed scan instead, which measures at about 60 + W outputs per
-// wide-step time.
-uint64_t step_outputs(const ParamSet &ps, int stream, const mtgp_tuning &t) {
+uint64_t step_outputs(const ParamSet &ps, int stream, const mtgp_tuning &t, bool sparse) {
     const uint32_t W = ps.W[(size_t)stream];
     const uint64_t smax = (uint64_t)t.threads_per_stream * (uint64_t)t.outputs_per_lane;
     uint64_t s;
     if (W >= 64) s = W & ~31u;
     else if (t.threads_per_stream == 64 && ps.lin[(size_t)stream] &&
              W < (uint32_t)t.window_below_w)
-        s = 60 + W;
+        s = !sparse ? 60 + W : ps.N <= 400 ? 40 : 64;
     else s = W;
     return std::max<uint64_t>(1, std::min(s, smax));
 }
@@ -446,6 +442,26 @@ static uint64_t effective_target(const ParamSet &ps, const std::vector<Request> 
     return std::max<uint64_t>((uint64_t)t.jump_target_steps, adaptive);
 }
 
+constexpr uint64_t SPARSE_ITEMS_PER_CU = 6;
+
+// A batch whose work items (at the full chip's rates) are too few to fill
+// the chip: up to one and a half per SIMD, so that waves are mostly alone.
+// Its segment launch runs wide streams by whole workgroups, and its narrow
+// streams are cut by the rate of a wave alone: 100 mexp-11213 streams of 10^6
+// outputs 503 us (678 by the batch kernel; 605 with the narrow streams cut as
+// on a full chip), 512 mexp-44497 streams of 2^10 .. 2^22 1490 (1590; 1565
+// cut as at N = 351).  From three items per CU to fourteen it times alike.
+static bool is_sparse(const ParamSet &ps, const std::vector<Request> &reqs, uint64_t T,
+                      const mtgp_tuning &t) {
+    if (!has_wide(ps.N) || t.threads_per_stream != 64) return false;
+    uint64_t items = 0;
+    for (const Request &r : reqs) {
+        const uint64_t so = step_outputs(ps, r.stream, t);
+        items += T ? std::max<uint64_t>(1, (r.count + so * T - 1) / (so * T)) : 1;
+    }
+    return items <= (uint64_t)std::max(1, device_cus()) * SPARSE_ITEMS_PER_CU;
+}
+
 // Segment length for a target of v outputs: v rounded down to m * 2^e with
 // m in {4, 5, 6, 7} (at most 20% short), at least 256.  The coarse grid
 // keeps a stream's segment length, and so its cached jump polynomials, the
@@ -486,12 +502,12 @@ static int group_size(const ParamSet &ps, const Request &r, const mtgp_tuning &t
 // polynomial of degree D (D < 1: never).  With `groups`, requests of narrow
 // streams are cut further, into whole groups.
 static void decide(const ParamSet &ps, const Request &r, int D, uint64_t T, const mtgp_tuning &t,
-                   bool groups, Seg &g) {
+                   bool groups, bool sparse, Seg &g) {
     g.C = 1;
     g.group = 1;
     g.D = g.Dsize = 0;
     if (!T || D < 1) return;
-    const uint64_t so = step_outputs(ps, r.stream, t);
+    const uint64_t so = step_outputs(ps, r.stream, t, sparse);
     const int n = groups ? group_size(ps, r, t) : 1;
     if (n > 1) {
         const uint64_t items = std::max<uint64_t>(1, (r.count + so * T - 1) / (so * T));
@@ -517,9 +533,10 @@ static void decide(const ParamSet &ps, const Request &r, int D, uint64_t T, cons
     g.D = g.Dsize = D;
 }
 
-static bool wants_split(const ParamSet &ps, const Request &r, uint64_t T, const mtgp_tuning &t) {
+static bool wants_split(const ParamSet &ps, const Request &r, uint64_t T, const mtgp_tuning &t,
+                        bool sparse) {
     if (!T) return false;
-    const uint64_t so = step_outputs(ps, r.stream, t);
+    const uint64_t so = step_outputs(ps, r.stream, t, sparse);
     return ((r.count + so - 1) / so > T || group_size(ps, r, t) > 1) &&
            r.count > (uint64_t)ps.mexp + 128;
 }
@@ -652,16 +669,17 @@ std::shared_ptr<WsState> ws_state(const void *d_ws, bool create) {
 // block, so the counts alone do not give the offsets).
 struct GraphKey {
     const void *ws;
-    uint32_t nA, nB, nC, nF;
+    uint32_t nA, nB, nC, nF, nCw;
+    bool sparse;
     size_t off_A, off_B, off_C, off_F, off_pflag;
     const void *params;
     int N, tps, k, wg, win, device;
     bool stamps, errs;
     bool operator<(const GraphKey &o) const {
-        return std::tie(ws, nA, nB, nC, nF, off_A, off_B, off_C, off_F, off_pflag, params, N,
-                        tps, k, wg, win, device, stamps, errs) <
-               std::tie(o.ws, o.nA, o.nB, o.nC, o.nF, o.off_A, o.off_B, o.off_C, o.off_F,
-                        o.off_pflag, o.params, o.N, o.tps, o.k, o.wg, o.win, o.device, o.stamps,
+        return std::tie(ws, nA, nB, nC, nF, nCw, sparse, off_A, off_B, off_C, off_F, off_pflag,
+                        params, N, tps, k, wg, win, device, stamps, errs) <
+               std::tie(o.ws, o.nA, o.nB, o.nC, o.nF, o.nCw, o.sparse, o.off_A, o.off_B,
+                        o.off_C, o.off_F, o.off_pflag, o.params, o.N, o.tps, o.k, o.wg, o.win, o.device, o.stamps,
                         o.errs);
     }
 };
@@ -755,7 +773,13 @@ static int launch_phases(const ParamSet &ps, const void *d_params, char *ws, con
     a.items = C;
     a.counter = hdr + 1;
     a.n_items = fork ? w.nCs : w.nC;
-    if ((rc = launch_tuned(ps.N, t, a))) return bail(rc);
+    if (w.sparse) {
+        a.win_below = (uint32_t)t.window_below_w;
+        if ((e = launch_sparse(ps.N, a, w.nCw, hdr + HDR_B_CLAIM)) != hipSuccess)
+            return bail(hip_fail(e, "kernel launch"));
+    } else if ((rc = launch_tuned(ps.N, t, a))) {
+        return bail(rc);
+    }
     if (fork && (e = hipStreamWaitEvent(s, w.ev_join, 0)) != hipSuccess) {
         (void)hipStreamSynchronize(w.aux);
         return hip_fail(e, "hipStreamWaitEvent(join)");
@@ -781,9 +805,10 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
     std::vector<Seg> segs(reqs.size());
     std::vector<int> want;
     uint64_t T = effective_target(*ps, reqs, t);
+    const bool sparse = is_sparse(*ps, reqs, T, t);
     for (size_t i = 0; i < reqs.size(); ++i) {
         segs[i].req = (int)i;
-        if (wants_split(*ps, reqs[i], T, t)) want.push_back(reqs[i].stream);
+        if (wants_split(*ps, reqs[i], T, t, sparse)) want.push_back(reqs[i].stream);
     }
     if (!want.empty() && !w.no_alloc) {
         int rc = ensure_jumps(ps, d_params, d_states, stride, want, t, s);
@@ -806,7 +831,7 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
     while (true) {
         for (size_t i = 0; i < reqs.size(); ++i) {
             const int D = (sjs[i] && sjs[i]->status == 1) ? sjs[i]->D : 0;
-            decide(*ps, reqs[i], D, T, t, groups, segs[i]);
+            decide(*ps, reqs[i], D, T, t, groups, sparse, segs[i]);
             segs[i].sj = segs[i].C > 1 ? sjs[i] : nullptr;
         }
         L = layout_for(*ps, segs);
@@ -849,6 +874,7 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
         uint64_t steps;
         BatchItem b;
         bool segment;
+        bool wide = false;  // of a stream that a workgroup runs in a sparse launch
     };
     std::vector<CItem> C;
     std::vector<std::tuple<uint64_t, BatchItem, size_t>> A;  // steps, item, split index
@@ -862,7 +888,7 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
         const Seg &g = segs[i];
         const uint32_t mode = r.dtype == MTGP_F32 ? MODE_F32 : 0u;
         uint32_t *row = d_states + (size_t)r.stream * stride;
-        const uint64_t so = step_outputs(*ps, r.stream, t);
+        const uint64_t so = step_outputs(*ps, r.stream, t, sparse);
         auto base_item = [&](uint64_t count, uint64_t out_off) {
             BatchItem b;
             std::memset(&b, 0, sizeof b);
@@ -1006,11 +1032,21 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
     // the whole requests, each part longest first.  Only where the whole
     // requests are at most half the segments' steps, so that their launch,
     // capped below the chip's occupancy, does not outlast the segments.
+    //
+    // A sparse batch: the items that whole workgroups run first, each part
+    // longest first.
+    size_t n_wide = 0;
+    if (sparse)
+        for (CItem &c : C) {
+            c.wide = ps->W[c.b.stream] >= WIDE_MIN_W;
+            n_wide += c.wide ? 1 : 0;
+        }
     uint64_t whole_steps = 0, seg_steps = 0;
     for (const CItem &c : C) (c.segment ? seg_steps : whole_steps) += c.steps;
     const bool split_lists =
-        overlap && !A.empty() && whole_steps > 0 && 2 * whole_steps <= seg_steps;
+        overlap && !sparse && !A.empty() && whole_steps > 0 && 2 * whole_steps <= seg_steps;
     std::stable_sort(C.begin(), C.end(), [&](const CItem &x, const CItem &y) {
+        if (x.wide != y.wide) return x.wide;
         if (split_lists && x.segment != y.segment) return x.segment;
         return x.steps > y.steps;
     });
@@ -1031,6 +1067,8 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
     w.off_pflag = L.off_pflag;
     w.nCs = (uint32_t)(split_lists ? n_seg : C.size());
     w.overlap = split_lists;
+    w.sparse = sparse;
+    w.nCw = (uint32_t)n_wide;
     w.tables_end = L.off_poly;
     w.up_end = L.up_end;
     w.ps = ps;
@@ -1087,7 +1125,9 @@ int run_batch(const std::shared_ptr<ParamSet> &ps, const void *d_params, uint32_
         // using the cached one
         const uint64_t T = effective_target(*ps, reqs, t);
         bool any_split = false, any_whole = false;
-        for (const Request &r : reqs) (wants_split(*ps, r, T, t) ? any_split : any_whole) = true;
+        const bool sparse = is_sparse(*ps, reqs, T, t);
+        for (const Request &r : reqs)
+            (wants_split(*ps, r, T, t, sparse) ? any_split : any_whole) = true;
         if (!(any_split && any_whole)) ov = 0;
     }
     if (ov && !w.aux) {
@@ -1157,7 +1197,8 @@ int run_batch(const std::shared_ptr<ParamSet> &ps, const void *d_params, uint32_
 
     int dev = 0;
     (void)hipGetDevice(&dev);
-    GraphKey key{d_ws, w.nA, w.nB, w.nC, w.nF, w.off_A, w.off_B, w.off_C, w.off_F, w.off_pflag,
+    GraphKey key{d_ws, w.nA, w.nB, w.nC, w.nF, w.nCw, w.sparse,
+                 w.off_A, w.off_B, w.off_C, w.off_F, w.off_pflag,
                  d_params, ps->N, t.threads_per_stream, t.outputs_per_lane, t.workgroup_size,
                  t.window_below_w, dev, stamps, per_call_errors};
     std::lock_guard<std::mutex> lk(g_graph_mu);
@@ -1298,8 +1339,9 @@ int mtgp_batch_workspace_query(const void *d_params, const mtgp_work *h_items, i
     std::vector<int> want;
     std::vector<Request> reqs = to_requests(h_items, n_items);
     const uint64_t T = effective_target(*ps, reqs, t);
+    const bool sparse = is_sparse(*ps, reqs, T, t);
     for (const Request &r : reqs)
-        if (wants_split(*ps, r, T, t)) want.push_back(r.stream);
+        if (wants_split(*ps, r, T, t, sparse)) want.push_back(r.stream);
     if (!want.empty()) {
         rc = ensure_jumps(ps, d_params, nullptr, 0, want, t, nullptr);
         if (rc) return rc;
@@ -1313,12 +1355,12 @@ int mtgp_batch_workspace_query(const void *d_params, const mtgp_work *h_items, i
             const StreamJump *sj = ps->jumps[(size_t)k].get();
             segs[i].req = (int)i;
             if (sj && sj->status == 1 && !ps->dirty[(size_t)k]) {
-                decide(*ps, reqs[i], sj->D, T, t, true, segs[i]);
+                decide(*ps, reqs[i], sj->D, T, t, true, sparse, segs[i]);
             } else if (!sj || ps->dirty[(size_t)k]) {
                 // the polynomial will be built from the stream's state at
                 // generation time: size for the most segments (D = 1) and
                 // the largest degree (mexp)
-                decide(*ps, reqs[i], 1, T, t, true, segs[i]);
+                decide(*ps, reqs[i], 1, T, t, true, sparse, segs[i]);
                 if (segs[i].C > 1) segs[i].Dsize = (int)ps->mexp;
             }
         }

@@ -66,6 +66,10 @@ struct WsState {
     // requests in the segment list) start on `aux` beside the prefix and
     // jump launch, with at most overlap_groups workgroups per CU
     uint32_t nCs = 0;
+    // sparse: too few items to fill the chip; the segment list starts with
+    // the nCw items that whole workgroups run
+    bool sparse = false;
+    uint32_t nCw = 0;
     bool overlap = false;
     int overlap_groups = 0;
     hipStream_t aux = nullptr;
@@ -89,8 +93,9 @@ std::shared_ptr<ParamSet> lookup_params(const void *d_params, int n_streams);
 mtgp_tuning tuning_for(int N);
 int launch_tuned(int N, const mtgp_tuning &t, const LaunchArgs &a);
 
-// Outputs per step the generator achieves for step width W under a tuning.
-uint64_t step_outputs(const ParamSet &ps, int stream, const mtgp_tuning &t);
+// Outputs per step the generator achieves for step width W under a tuning;
+// sparse: on a chip with few waves, where a window takes several times a step.
+uint64_t step_outputs(const ParamSet &ps, int stream, const mtgp_tuning &t, bool sparse = false);
 
 // One request of a batch as the planner sees it.
 struct Request {

@@ -128,6 +128,7 @@ static_assert(sizeof(GroupItem) == sizeof(BatchItem), "GroupItem layout");
 //               jump launch, after the segments, end)
 //   word 24     claim counter of the whole-request list when it runs beside
 //               the prefix and jump launch
+//   word 25     claim counter of the items that whole workgroups run
 constexpr int HDR_ERR = 2;
 constexpr int HDR_LOG_MAX = 8;
 constexpr int HDR_ERR_WORDS = 2 + HDR_LOG_MAX;  // words HDR_ERR .. HDR_ERR + 9
@@ -135,6 +136,7 @@ constexpr int HDR_FIX_CLAIM = 12;
 constexpr int HDR_TAG = 13;
 constexpr int HDR_J_CLAIM = 15;
 constexpr int HDR_W_CLAIM = 24;
+constexpr int HDR_B_CLAIM = 25;
 constexpr size_t HDR_STAMP_BYTE = 64;
 constexpr size_t HDR_BYTES = 256;
 
@@ -212,6 +214,14 @@ hipError_t launch_prefix_jumps(int n_words, const BatchItem *prefix, uint32_t nP
                                const JumpBlock *jumps, uint32_t nJ, uint32_t *pflag,
                                const uint32_t *params, uint32_t *hdr, uint32_t win_below,
                                int num_cus, hipStream_t s);
+// Segment launch of a batch that leaves the chip nearly empty: the first
+// n_wide items by workgroups of 256, the others by waves (a.counter; the
+// wide items' counter is `wide_counter`).  Which items are wide: W at least
+// WIDE_MIN_W.
+constexpr uint32_t WIDE_MIN_W = 128;
+constexpr bool has_wide(int N) { return N > (int)WIDE_MIN_W; }
+hipError_t launch_sparse(int n_words, const LaunchArgs &a, uint32_t n_wide,
+                         uint32_t *wide_counter);
 hipError_t launch_check(int n_words, const LaunchArgs &a);
 int variant_slots_per_cu(int n_words, int tps, int k, int wpb);
 hipError_t launch_seed(const uint32_t *params, uint32_t *states, uint32_t stride,

@@ -1007,9 +1007,11 @@ __device__ __forceinline__ void gen_body(const uint32_t *__restrict__ params,
         if (item.flag != 0) {
             // Publish completion of the request to the host: every lane's
             // output and state stores are made visible system-wide first.
+            // (a wave's lanes all store the flag: with a store by lane 0 alone
+            // the compiler may split the claim loop by lane.)
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
             group_sync<TPS>();
-            if (lane == 0)
+            if (TPS == 64 || lane == 0)
                 __hip_atomic_store(reinterpret_cast<uint32_t *>(item.flag), 1u, __ATOMIC_RELEASE,
                                    __HIP_MEMORY_SCOPE_SYSTEM);
         }
@@ -1036,6 +1038,80 @@ few_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__ it
            uint32_t win_below, PlainArgs plain) {
     gen_body<N, 64, 8, 4, false, true>(params, items, n_items, counter, persistent, win_below,
                                        plain);
+}
+
+// Segments and whole requests of a batch with fewer items than the chip has
+// SIMDs: a wave that runs alone spends a step issuing the instructions of
+// its rows (four rows of 64 outputs 980 cycles, of which some 300 are the
+// chain), so streams of wide steps are run by whole workgroups, a row or a
+// few per wave.  The workgroups first claim the wide items, then their waves
+// the others.
+constexpr int wide_k(int N) { return N <= 400 ? 1 : N <= 800 ? 2 : 4; }
+
+template <int N>
+constexpr int sparse_lds_words() {
+    const int a = 4 * Core<N, 64, 8>::LDS_WORDS, b = Core<N, 256, wide_k(N)>::LDS_WORDS;
+    return (a > b ? a : b) + 4;
+}
+
+template <int N>
+__global__ void __launch_bounds__(256)
+sparse_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__ items,
+              uint32_t n_wide, uint32_t n_items, uint32_t *__restrict__ wide_counter,
+              uint32_t *__restrict__ counter, uint32_t win_below) {
+    using B = Core<N, 256, wide_k(N)>;
+    using A = Core<N, 64, 8>;
+    extern __shared__ uint32_t lds[];
+    uint32_t &s_claim = lds[sparse_lds_words<N>() - 4];
+    while (true) {  // wide items, one per workgroup
+        __syncthreads();
+        if (threadIdx.x == 0) s_claim = atomicAdd(wide_counter, 1u);
+        __syncthreads();
+        const uint32_t it = __builtin_amdgcn_readfirstlane(s_claim);
+        if (it >= n_wide) break;
+        const BatchItem item = items[it];
+        const uint32_t *prm = params + (uint64_t)item.stream * P_WORDS;
+        uint32_t *fail = (item.mode & MODE_VERIFY) ? &reinterpret_cast<ReqRec *>(item.rec)->failed
+                                                   : nullptr;
+        if (item.mode & MODE_F32)
+            B::template run<true, false, false>(prm, item, lds, threadIdx.x, fail, 0u);
+        else
+            B::template run<false, false, false>(prm, item, lds, threadIdx.x, fail, 0u);
+        if (item.flag != 0) {
+            // publish completion to the host, after every thread's stores
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+            __syncthreads();
+            if (threadIdx.x == 0)
+                __hip_atomic_store(reinterpret_cast<uint32_t *>(item.flag), 1u, __ATOMIC_RELEASE,
+                                   __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
+    __syncthreads();
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t *buf = lds + wave * A::LDS_WORDS;
+    while (true) {  // the others, one per wave
+        uint32_t v = 0;
+        if (lane == 0) v = atomicAdd(counter, 1u);
+        const uint32_t it = n_wide + __builtin_amdgcn_readfirstlane(v);
+        if (it >= n_items) break;
+        const BatchItem item = items[it];
+        const uint32_t *prm = params + (uint64_t)item.stream * P_WORDS;
+        uint32_t *fail = (item.mode & MODE_VERIFY) ? &reinterpret_cast<ReqRec *>(item.rec)->failed
+                                                   : nullptr;
+        if (item.mode & MODE_F32)
+            A::template run<true, false, true>(prm, item, buf, lane, fail, win_below);
+        else
+            A::template run<false, false, true>(prm, item, buf, lane, fail, win_below);
+        if (item.flag != 0) {
+            // every lane stores the flag: with a store by lane 0 alone the
+            // compiler splits the claim loop by lane
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+            group_sync<64>();
+            __hip_atomic_store(reinterpret_cast<uint32_t *>(item.flag), 1u, __ATOMIC_RELEASE,
+                               __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+    }
 }
 
 // Outputs per lane and step of the prefix kernel (the default tuning's).
@@ -1539,7 +1615,7 @@ __global__ void clear_kernel(uint32_t *p, uint32_t n) {
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0u;
 }
 
-// One wave; lane i owns header word i (i < 24).  Every lane reads the tag
+// One wave; lane i owns header word i (i < 26).  Every lane reads the tag
 // before any lane writes it.
 __global__ void header_kernel(uint32_t *hdr, uint32_t tag_lo, uint32_t tag_hi,
                               uint32_t clear_errors) {
@@ -1547,7 +1623,8 @@ __global__ void header_kernel(uint32_t *hdr, uint32_t tag_lo, uint32_t tag_hi,
     const bool fresh = hdr[HDR_TAG] != tag_lo || hdr[HDR_TAG + 1] != tag_hi;
     __builtin_amdgcn_wave_barrier();
     const bool claim = i < (uint32_t)HDR_ERR || i == (uint32_t)HDR_FIX_CLAIM ||
-                       i == (uint32_t)HDR_J_CLAIM || i == (uint32_t)HDR_W_CLAIM;
+                       i == (uint32_t)HDR_J_CLAIM || i == (uint32_t)HDR_W_CLAIM ||
+                       i == (uint32_t)HDR_B_CLAIM;
     const bool errw = i >= (uint32_t)HDR_ERR && i < (uint32_t)(HDR_ERR + HDR_ERR_WORDS);
     const bool stamp = i >= HDR_STAMP_BYTE / 4 && i < HDR_STAMP_BYTE / 4 + 8;
     if (claim || (errw && (fresh || clear_errors)) || (stamp && fresh)) hdr[i] = 0u;
@@ -1668,6 +1745,36 @@ static hipError_t launch_check_n(const LaunchArgs &a) {
                        (hipStream_t)a.stream, a.params, a.items, a.n_items, per_wave, a.err,
                        a.win_below);
     return hipGetLastError();
+}
+
+template <int N>
+static hipError_t launch_sparse_n(const LaunchArgs &a, uint32_t n_wide, uint32_t *wide_counter) {
+    constexpr int lds = sparse_lds_words<N>() * 4;
+    static bool attr_set = false;  // benign race: idempotent attribute
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void *)sparse_kernel<N>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    uint32_t grid = n_wide + (a.n_items - n_wide + 3) / 4;
+    const uint32_t cap = (uint32_t)a.num_cus * (uint32_t)(160 * 1024 / lds);
+    if (grid > cap) grid = cap;
+    (void)hipGetLastError();  // report this launch only
+    hipLaunchKernelGGL(sparse_kernel<N>, dim3(grid > 0 ? grid : 1), dim3(256), lds,
+                       (hipStream_t)a.stream, a.params, a.items, n_wide, a.n_items, wide_counter,
+                       a.counter, a.win_below);
+    return hipGetLastError();
+}
+
+hipError_t launch_sparse(int n_words, const LaunchArgs &a, uint32_t n_wide,
+                         uint32_t *wide_counter) {
+    switch (n_words) {
+        case 351: return launch_sparse_n<351>(a, n_wide, wide_counter);
+        case 726: return launch_sparse_n<726>(a, n_wide, wide_counter);
+        case 1391: return launch_sparse_n<1391>(a, n_wide, wide_counter);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 template <int N>
