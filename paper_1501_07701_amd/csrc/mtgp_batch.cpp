@@ -788,7 +788,6 @@ static int launch_phases(const ParamSet &ps, const void *d_params, char *ws, con
     if (w.nF) {  // request checks of the split requests
         a.items = (const BatchItem *)(ws + w.off_F);
         a.n_items = w.nF;
-        a.counter = hdr + HDR_FIX_CLAIM;
         a.win_below = (uint32_t)t.window_below_w;
         if ((e = launch_check(ps.N, a)) != hipSuccess) return hip_fail(e, "check kernel");
     }

@@ -119,7 +119,7 @@ static_assert(sizeof(GroupItem) == sizeof(BatchItem), "GroupItem layout");
 //   word 2      requests regenerated after a failed segment check
 //   word 3      entries written to the log (may exceed HDR_LOG_MAX)
 //   word 4..11  stream ids of the first HDR_LOG_MAX such requests
-//   word 12     claim counter of the request-check launch
+//   word 12     unused
 //   word 13, 14 tag: a 64-bit value derived from the workspace address; a
 //               header without it (fresh or reused memory) is cleared by
 //               the first launch of the next call
@@ -132,7 +132,6 @@ static_assert(sizeof(GroupItem) == sizeof(BatchItem), "GroupItem layout");
 constexpr int HDR_ERR = 2;
 constexpr int HDR_LOG_MAX = 8;
 constexpr int HDR_ERR_WORDS = 2 + HDR_LOG_MAX;  // words HDR_ERR .. HDR_ERR + 9
-constexpr int HDR_FIX_CLAIM = 12;
 constexpr int HDR_TAG = 13;
 constexpr int HDR_J_CLAIM = 15;
 constexpr int HDR_W_CLAIM = 24;
@@ -200,9 +199,9 @@ hipError_t launch_variant(int n_words, int tps, int k, int wpb, const LaunchArgs
 // Jump blocks alone (their raw words are there), for state length n_words.
 hipError_t launch_jump(int n_words, const JumpBlock *blocks, uint32_t n_blocks, int num_cus,
                        hipStream_t s);
-// Persistent launches of the prefix kernel (items may carry MODE_RAW) and
-// of the request-check kernel (MODE_FIXUP items) for state length n_words
-// (one wave per item; a.win_below applies).
+// Launches of the prefix kernel (persistent; items may carry MODE_RAW) and,
+// below, of the request-check kernel (MODE_FIXUP items) for state length
+// n_words (a.win_below applies).
 hipError_t launch_prefix(int n_words, const LaunchArgs &a);
 // Plain calls of few streams (one wave per stream, a.win_below applies).
 hipError_t launch_few(int n_words, const LaunchArgs &a);

@@ -17,7 +17,7 @@
 // reaches the end of the buffer the last N words are copied to the front.
 //
 // Jump-ahead.  A work item may start from any state: a long stream is cut
-// into segments whose start states jump_kernel computes from the stream's
+// into segments whose start states jump_block computes from the stream's
 // first words (the generator is GF(2)-linear, so the state J outputs ahead
 // is a fixed XOR-combination of consecutive words, given by x^(J-1) mod p
 // for a polynomial p that annihilates the word sequence).  Each segment
@@ -1622,9 +1622,8 @@ __global__ void header_kernel(uint32_t *hdr, uint32_t tag_lo, uint32_t tag_hi,
     const uint32_t i = threadIdx.x;
     const bool fresh = hdr[HDR_TAG] != tag_lo || hdr[HDR_TAG + 1] != tag_hi;
     __builtin_amdgcn_wave_barrier();
-    const bool claim = i < (uint32_t)HDR_ERR || i == (uint32_t)HDR_FIX_CLAIM ||
-                       i == (uint32_t)HDR_J_CLAIM || i == (uint32_t)HDR_W_CLAIM ||
-                       i == (uint32_t)HDR_B_CLAIM;
+    const bool claim = i < (uint32_t)HDR_ERR || i == (uint32_t)HDR_J_CLAIM ||
+                       i == (uint32_t)HDR_W_CLAIM || i == (uint32_t)HDR_B_CLAIM;
     const bool errw = i >= (uint32_t)HDR_ERR && i < (uint32_t)(HDR_ERR + HDR_ERR_WORDS);
     const bool stamp = i >= HDR_STAMP_BYTE / 4 && i < HDR_STAMP_BYTE / 4 + 8;
     if (claim || (errw && (fresh || clear_errors)) || (stamp && fresh)) hdr[i] = 0u;
