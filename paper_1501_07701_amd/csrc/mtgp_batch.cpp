@@ -804,7 +804,7 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
     std::vector<Seg> segs(reqs.size());
     std::vector<int> want;
     uint64_t T = effective_target(*ps, reqs, t);
-    const bool sparse = is_sparse(*ps, reqs, T, t);
+    const bool sparse = !w.shared_chip && is_sparse(*ps, reqs, T, t);
     for (size_t i = 0; i < reqs.size(); ++i) {
         segs[i].req = (int)i;
         if (wants_split(*ps, reqs[i], T, t, sparse)) want.push_back(reqs[i].stream);

@@ -70,6 +70,10 @@ struct WsState {
     // the nCw items that whole workgroups run
     bool sparse = false;
     uint32_t nCw = 0;
+    // several batches share the chip (the server's slots): no batch is
+    // planned as sparse, whatever its own items, so that a stream's segment
+    // length, and with it its cached powers, stays the same between batches
+    bool shared_chip = false;
     bool overlap = false;
     int overlap_groups = 0;
     hipStream_t aux = nullptr;

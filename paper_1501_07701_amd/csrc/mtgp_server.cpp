@@ -227,6 +227,7 @@ int mtgp_server_create(const void *d_params, uint32_t *d_states, int state_strid
     for (int i = 0; i < o.max_inflight_batches; ++i) {
         Slot &sl = B.slots[(size_t)i];
         sl.wst = std::make_unique<WsState>();
+        sl.wst->shared_chip = true;
         sl.d_ws = (char *)d_pool + (size_t)i * ws;
         hipError_t e = hipStreamCreateWithFlags(&sl.hs, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&sl.done, hipEventDisableTiming);
