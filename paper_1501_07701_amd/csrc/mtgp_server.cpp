@@ -124,15 +124,13 @@ class HipBackend final : public SchedBackend {
                 return hip_fail(e, "hipStreamCreate(result copies)");
             }
         }
-        // one launch for all results that lie in this GPU's memory; others
-        // (another GPU's, mapped host memory) by a copy command each
+        // one launch for all results whose destination lies in one allocation
+        // of this GPU; others (another GPU's, mapped host memory) by a copy
+        // command each, which refuses a destination that is too short
         int rc = MTGP_OK;
         std::vector<CopyPiece> pieces;
         for (const Copy &c : copies) {
-            hipPointerAttribute_t at{};
-            const bool here = hipPointerGetAttributes(&at, c.dst) == hipSuccess &&
-                              at.type == hipMemoryTypeDevice && at.device == device;
-            if (here) {
+            if (fits_here(c.dst, c.bytes)) {
                 const uint64_t src = (uint64_t)(uintptr_t)(d_pool + c.off),
                                dst = (uint64_t)(uintptr_t)c.dst;
                 for (uint64_t o = 0; o < c.bytes; o += COPY_PIECE)
@@ -140,7 +138,6 @@ class HipBackend final : public SchedBackend {
                                                std::min<uint64_t>(COPY_PIECE, c.bytes - o)});
                 continue;
             }
-            (void)hipGetLastError();  // the attribute query's
             hipError_t e = hipMemcpyAsync(c.dst, d_pool + c.off, c.bytes, hipMemcpyDeviceToDevice,
                                           copy_stream_);
             if (e != hipSuccess && rc == MTGP_OK) rc = hip_fail(e, "hipMemcpyAsync(kept result)");
@@ -170,6 +167,20 @@ class HipBackend final : public SchedBackend {
     }
 
    private:
+    // Whether [dst, dst + bytes) lies in one allocation of this GPU's memory.
+    bool fits_here(void *dst, uint64_t bytes) const {
+        hipPointerAttribute_t at{};
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if (hipPointerGetAttributes(&at, dst) != hipSuccess || at.type != hipMemoryTypeDevice ||
+            at.device != device || hipMemGetAddressRange(&base, &size, dst) != hipSuccess) {
+            (void)hipGetLastError();  // the queries'
+            return false;
+        }
+        const uint64_t off = (uint64_t)((char *)dst - (char *)base);
+        return off <= size && bytes <= size - off;
+    }
+
     std::mutex copy_mu_;
     hipStream_t copy_stream_ = nullptr;
     CopyPiece *copy_list_ = nullptr;  // pinned, host-mapped
