@@ -43,6 +43,24 @@ struct Slot {
     std::unique_ptr<WsState> wst;
 };
 
+// Makes `device` current for a scope.
+class DeviceScope {
+   public:
+    explicit DeviceScope(int device) {
+        if (hipGetDevice(&before_) != hipSuccess) before_ = device;
+        if (before_ != device) (void)hipSetDevice(device);
+        device_ = device;
+    }
+    ~DeviceScope() {
+        if (before_ != device_) (void)hipSetDevice(before_);
+    }
+    DeviceScope(const DeviceScope &) = delete;
+    DeviceScope &operator=(const DeviceScope &) = delete;
+
+   private:
+    int before_ = 0, device_ = 0;
+};
+
 // The device side of the scheduler: plans and launches batches through the
 // batch planner on per-slot HIP streams, reads completion flags and the
 // repair words, copies kept results.
@@ -117,6 +135,9 @@ class HipBackend final : public SchedBackend {
 
     int copy_out(const std::vector<Copy> &copies) override {
         std::lock_guard<std::mutex> lk(copy_mu_);
+        // a client's thread, whose current GPU may be another: the copy
+        // stream and the copy kernel belong to the server's
+        DeviceScope on(device);
         if (!copy_stream_) {
             hipError_t e = hipStreamCreateWithFlags(&copy_stream_, hipStreamNonBlocking);
             if (e != hipSuccess) {
