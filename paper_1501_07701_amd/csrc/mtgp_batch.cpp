@@ -56,10 +56,7 @@ struct StreamJump {
     int D = 0;       // degree of the annihilating polynomial p
     bool has_seed_orbit = false;  // p annihilates the seed status's orbit
     std::unique_ptr<poly::Modulus> mod;
-    uint64_t lseg = 0;                       // segment length g is built for
-    poly::Poly xl;                           // x^lseg mod p
-    std::vector<std::vector<uint32_t>> g;    // g[c-1] = x^(c*lseg-1) mod p, packed
-    std::mutex mu;
+    poly::Powers powers;          // x^(c*lseg-1) mod p by segment length
 };
 
 Staging::~Staging() {
@@ -134,16 +131,6 @@ uint64_t step_outputs(const ParamSet &ps, int stream, const mtgp_tuning &t, bool
         s = !sparse ? 60 + W : ps.N <= 400 ? 40 : 64;
     else s = W;
     return std::max<uint64_t>(1, std::min(s, smax));
-}
-
-static std::vector<uint32_t> pack32(const poly::Poly &p, int nbits) {
-    std::vector<uint32_t> w((size_t)(nbits + 31) / 32, 0u);
-    for (size_t i = 0; i < w.size(); ++i) {
-        const uint64_t v = (i / 2 < p.size()) ? p[i / 2] : 0;
-        w[i] = (uint32_t)(v >> (32 * (i & 1)));
-    }
-    if (nbits & 31) w.back() &= (1u << (nbits & 31)) - 1u;
-    return w;
 }
 
 // lcm of the annihilators of the bit sequences parity(x_t & r), t >= 1.
@@ -280,7 +267,7 @@ static int ensure_jumps(const std::shared_ptr<ParamSet> &ps, const void *d_param
                 if (ok[j]) continue;
                 const int D = poly::degree(P[j]);
                 if (D < 1 || D > mexp) continue;
-                const std::vector<uint32_t> w = pack32(P[j], D + 1);
+                const std::vector<uint32_t> w = poly::pack32(P[j], D + 1);
                 std::memcpy(&pw[(size_t)nj * PW], w.data(), w.size() * 4);
                 for (int v0 = 0; v0 < mexp; v0 += vwords) {
                     JumpBlock jb;
@@ -351,39 +338,6 @@ static int ensure_jumps(const std::shared_ptr<ParamSet> &ps, const void *d_param
     return MTGP_OK;
 }
 
-// True when the stream's cached powers already serve segment length lseg
-// up to cmax.
-static bool g_ready(StreamJump &sj, uint64_t lseg, int cmax) {
-    std::lock_guard<std::mutex> lk(sj.mu);
-    return sj.lseg == lseg && (int)sj.g.size() >= cmax - 1;
-}
-
-// g[c-1] = x^(c*lseg-1) mod p for c = 1 .. cmax-1.
-static void ensure_g(StreamJump &sj, uint64_t lseg, int cmax) {
-    std::lock_guard<std::mutex> lk(sj.mu);
-    if (sj.lseg != lseg) {
-        sj.lseg = lseg;
-        sj.g.clear();
-        sj.xl = sj.mod->powx(lseg);
-    }
-    if ((int)sj.g.size() >= cmax - 1) return;
-    poly::Poly cur;
-    if (sj.g.empty()) {
-        cur = sj.mod->powx(lseg - 1);
-        sj.g.push_back(pack32(cur, sj.D));
-    } else {
-        // unpack the last one
-        const std::vector<uint32_t> &w = sj.g.back();
-        cur.assign((w.size() + 1) / 2, 0);
-        for (size_t i = 0; i < w.size(); ++i) cur[i / 2] |= (uint64_t)w[i] << (32 * (i & 1));
-        poly::trim(cur);
-    }
-    while ((int)sj.g.size() < cmax - 1) {
-        cur = sj.mod->mulmod(cur, sj.xl);
-        sj.g.push_back(pack32(cur, sj.D));
-    }
-}
-
 // ---------------------------------------------------------------- plan ----
 
 namespace {
@@ -399,6 +353,7 @@ struct Seg {
     int Dsize = 0;       // degree the workspace is sized for (>= D)
     int group = 1;       // segments per work item (2, 4 or 8: a group; then c0 = 1)
     std::shared_ptr<StreamJump> sj;
+    std::shared_ptr<const poly::PowerSet> powers;  // for c = 1 .. c0 + C - 2
 };
 
 struct Layout {
@@ -845,15 +800,16 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
     if (L.total > ws_bytes)
         return fail(MTGP_EINVAL, "workspace of %zu bytes too small (need %zu)", ws_bytes,
                     L.total);
-    // polynomials: only streams whose cache lacks them (a thread per
-    // stream costs more than a batch of cached lookups)
-    std::vector<Seg *> split;
+    // polynomials: threads only for streams whose cache lacks them (a thread
+    // per stream costs more than a batch of cached lookups)
+    std::vector<Seg *> missing;
+    auto powers_of = [](const Seg &g) { return (int)(g.c0 + (uint64_t)g.C - 2); };
     for (Seg &g : segs)
-        if (g.C > 1 && !g_ready(*g.sj, g.lseg, (int)(g.c0 + (uint64_t)g.C - 1)))
-            split.push_back(&g);
-    parallel_for((int)split.size(), [&](int i) {
-        const Seg &g = *split[i];
-        ensure_g(*g.sj, g.lseg, (int)(g.c0 + (uint64_t)g.C - 1));
+        if (g.C > 1 && !(g.powers = g.sj->powers.find(g.lseg, powers_of(g))))
+            missing.push_back(&g);
+    parallel_for((int)missing.size(), [&](int i) {
+        Seg &g = *missing[i];
+        g.powers = g.sj->powers.get(*g.sj->mod, g.lseg, powers_of(g));
     });
 
     // the image of [HDR_BYTES, up_end): item tables, request records,
@@ -968,7 +924,7 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
         const uint64_t polys = (uint64_t)(uintptr_t)(ws + poly_off);
         for (int k = 1; k < g.C; ++k) {
             const uint64_t c = g.c0 + (uint64_t)k - 1;
-            std::memcpy(at(poly_off), g.sj->g[(size_t)c - 1].data(), pw * 4);
+            std::memcpy(at(poly_off), g.powers->g[(size_t)c - 1].data(), pw * 4);
             poly_off += pw * 4;
         }
         for (int m0 = 0; m0 < N; m0 += jump_words(N)) {
@@ -1321,7 +1277,7 @@ int mtgp_stream_polynomials(const void *d_params, int n_streams, uint32_t *h_coe
             continue;
         }
         h_degrees[k] = sj->D;
-        const std::vector<uint32_t> w = pack32(sj->mod->p, sj->D + 1);
+        const std::vector<uint32_t> w = poly::pack32(sj->mod->p, sj->D + 1);
         std::memcpy(dst, w.data(), std::min(w.size(), (size_t)words_per_stream) * 4);
     }
     return MTGP_OK;

@@ -299,5 +299,93 @@ int berlekamp_massey(const uint8_t *bits, int n, Poly *annihilator) {
     return L;
 }
 
+std::vector<uint32_t> pack32(const Poly &p, int nbits) {
+    std::vector<uint32_t> w((size_t)(nbits + 31) / 32, 0u);
+    for (size_t i = 0; i < w.size(); ++i) {
+        const uint64_t v = (i / 2 < p.size()) ? p[i / 2] : 0;
+        w[i] = (uint32_t)(v >> (32 * (i & 1)));
+    }
+    if (nbits & 31) w.back() &= (1u << (nbits & 31)) - 1u;
+    return w;
+}
+
+static Poly unpack32(const std::vector<uint32_t> &w) {
+    Poly p((w.size() + 1) / 2, 0);
+    for (size_t i = 0; i < w.size(); ++i) p[i / 2] |= (uint64_t)w[i] << (32 * (i & 1));
+    trim(p);
+    return p;
+}
+
+static size_t set_bytes(const PowerSet &s) {
+    return s.g.empty() ? 0 : s.g.size() * s.g[0].size() * sizeof(uint32_t);
+}
+
+std::shared_ptr<PowerSet> Powers::front(uint64_t lseg) {
+    for (size_t i = 0; i < sets_.size(); ++i)
+        if (sets_[i]->lseg == lseg) {
+            std::rotate(sets_.begin(), sets_.begin() + (ptrdiff_t)i,
+                        sets_.begin() + (ptrdiff_t)i + 1);
+            return sets_.front();
+        }
+    return nullptr;
+}
+
+std::shared_ptr<const PowerSet> Powers::find(uint64_t lseg, int n) {
+    std::lock_guard<std::mutex> lk(mu_);
+    std::shared_ptr<PowerSet> s = front(lseg);
+    if (s && (int)s->g.size() < n) s = nullptr;
+    return s;
+}
+
+std::shared_ptr<const PowerSet> Powers::get(const Modulus &m, uint64_t lseg, int n) {
+    std::lock_guard<std::mutex> lk(mu_);
+    std::shared_ptr<PowerSet> s = front(lseg);
+    if (s && (int)s->g.size() >= n) return s;
+    // a set that was handed out stays as it is: the longer one is another
+    auto t = std::make_shared<PowerSet>();
+    t->lseg = lseg;
+    if (s) t->g = s->g;
+    Poly cur;
+    if (t->g.empty()) {
+        cur = m.powx(lseg - 1);
+        t->g.push_back(pack32(cur, m.d));
+        ++built_;
+    } else {
+        cur = unpack32(t->g.back());
+    }
+    if ((int)t->g.size() < n) {
+        const Poly xl = m.reduce(shl(unpack32(t->g[0]), 1));  // x^lseg
+        while ((int)t->g.size() < n) {
+            cur = m.mulmod(cur, xl);
+            t->g.push_back(pack32(cur, m.d));
+            ++built_;
+        }
+    }
+    if (s) sets_.front() = t;
+    else sets_.insert(sets_.begin(), t);
+    const size_t keep = std::max(POWERS_KEEP_BYTES, set_bytes(*t));
+    size_t others = 0;
+    for (size_t i = 1; i < sets_.size(); ++i) {
+        others += set_bytes(*sets_[i]);
+        if (others > keep) {
+            sets_.resize(i);
+            break;
+        }
+    }
+    return t;
+}
+
+size_t Powers::built() const {
+    std::lock_guard<std::mutex> lk(mu_);
+    return built_;
+}
+
+size_t Powers::bytes() const {
+    std::lock_guard<std::mutex> lk(mu_);
+    size_t n = 0;
+    for (const auto &s : sets_) n += set_bytes(*s);
+    return n;
+}
+
 }  // namespace poly
 }  // namespace mtgp
