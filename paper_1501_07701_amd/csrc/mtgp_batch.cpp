@@ -371,6 +371,33 @@ size_t batch_min_ws_bytes(int n_items) {
     return HDR_BYTES + al256((size_t)std::max(n_items, 0) * sizeof(BatchItem));
 }
 
+// Segments of a request that would run together on one wave: as many as its
+// step width allows (group_members), fewer for short requests, 1 = no group.
+// A member pays a jump, about the time of 4,000 outputs at N = 101, so it
+// gets at least 16,384.
+static bool group_path(const ParamSet &ps, const Request &r, const mtgp_tuning &t) {
+    return has_groups(ps.N) && t.threads_per_stream == 64 && ps.lin[(size_t)r.stream] &&
+           ps.W[(size_t)r.stream] < (uint32_t)t.window_below_w;
+}
+
+static int group_size(const ParamSet &ps, const Request &r, const mtgp_tuning &t) {
+    if (!group_path(ps, r, t)) return 1;
+    const uint32_t W = ps.W[(size_t)r.stream];
+    int n = group_members(W);
+    // (a group of W > 32 is whole: its rows are compiled for all members)
+    while (n > 1 && r.count < (uint64_t)n * 16384u) n = W > 32 ? 1 : n / 2;
+    return n;
+}
+
+// Whether any request of a batch is long enough to run in groups.
+static bool any_groups(const ParamSet &ps, const std::vector<Request> &reqs,
+                       const mtgp_tuning &t) {
+    if (!has_groups(ps.N)) return false;
+    for (const Request &r : reqs)
+        if (group_size(ps, r, t) > 1) return true;
+    return false;
+}
+
 // The dependent-step target of a batch: the tuning's jump_target_steps is
 // a floor (0 disables splitting); above it the target follows the batch's
 // balanced makespan, total steps over the streams the device runs at once,
@@ -385,7 +412,8 @@ static uint64_t effective_target(const ParamSet &ps, const std::vector<Request> 
         total += (r.count + so - 1) / so;
     }
     const int wpb = t.threads_per_stream == 64 ? t.workgroup_size / 64 : 1;
-    const int per_cu = variant_slots_per_cu(ps.N, t.threads_per_stream, t.outputs_per_lane, wpb);
+    const int per_cu = variant_slots_per_cu(ps.N, t.threads_per_stream, t.outputs_per_lane, wpb,
+                                            any_groups(ps, reqs, t));
     const uint64_t slots = (uint64_t)std::max(1, per_cu) * (uint64_t)std::max(1, device_cus());
     // a multiple of the balanced share of steps per resident stream: more,
     // shorter segments shorten the tail of the segment phase but every
@@ -433,24 +461,6 @@ static uint64_t segment_length(uint64_t v) {
 static uint64_t group_length(uint64_t v) {
     const int e = std::max(0, 63 - __builtin_clzll(v | 1) - 4);
     return ((v + (1ull << e) - 1) >> e) << e;
-}
-
-// Segments of a request that would run together on one wave: as many as its
-// step width allows (group_members), fewer for short requests, 1 = no group.
-// A member pays a jump, about the time of 4,000 outputs at N = 101, so it
-// gets at least 16,384.
-static bool group_path(const ParamSet &ps, const Request &r, const mtgp_tuning &t) {
-    return has_groups(ps.N) && t.threads_per_stream == 64 && ps.lin[(size_t)r.stream] &&
-           ps.W[(size_t)r.stream] < (uint32_t)t.window_below_w;
-}
-
-static int group_size(const ParamSet &ps, const Request &r, const mtgp_tuning &t) {
-    if (!group_path(ps, r, t)) return 1;
-    const uint32_t W = ps.W[(size_t)r.stream];
-    int n = group_members(W);
-    // (a group of W > 32 is whole: its rows are compiled for all members)
-    while (n > 1 && r.count < (uint64_t)n * 16384u) n = W > 32 ? 1 : n / 2;
-    return n;
 }
 
 // Splits a request when it needs more than T dependent steps, for a stream
@@ -625,17 +635,22 @@ std::shared_ptr<WsState> ws_state(const void *d_ws, bool create) {
 struct GraphKey {
     const void *ws;
     uint32_t nA, nB, nC, nF, nCw;
-    bool sparse;
+    bool sparse, groups;
     size_t off_A, off_B, off_C, off_F, off_pflag;
     const void *params;
     int N, tps, k, wg, win, device;
     bool stamps, errs;
     bool operator<(const GraphKey &o) const {
-        return std::tie(ws, nA, nB, nC, nF, nCw, sparse, off_A, off_B, off_C, off_F, off_pflag,
-                        params, N, tps, k, wg, win, device, stamps, errs) <
-               std::tie(o.ws, o.nA, o.nB, o.nC, o.nF, o.nCw, o.sparse, o.off_A, o.off_B,
-                        o.off_C, o.off_F, o.off_pflag, o.params, o.N, o.tps, o.k, o.wg, o.win, o.device, o.stamps,
-                        o.errs);
+        return key() < o.key();
+    }
+
+   private:
+    std::tuple<const void *, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, bool, bool, size_t,
+               size_t, size_t, size_t, size_t, const void *, int, int, int, int, int, int, bool,
+               bool>
+    key() const {
+        return {ws,    nA,    nB,      nC,     nF, nCw, sparse, groups, off_A, off_B,  off_C,
+                off_F, off_pflag, params, N, tps, k,   wg,     win,    device, stamps, errs};
     }
 };
 std::atomic<bool> g_stamps{false};  // phase timestamps in every batch call
@@ -689,6 +704,7 @@ static int launch_phases(const ParamSet &ps, const void *d_params, char *ws, con
     a.params = (const uint32_t *)d_params;
     a.err = hdr + HDR_ERR;
     a.persistent = true;
+    a.groups = w.groups;
     a.num_cus = device_cus();
     a.stream = s;
     const BatchItem *C = (const BatchItem *)(ws + w.off_C);
@@ -838,6 +854,8 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
     std::vector<int32_t> split_streams;
     size_t raw_off = L.off_raw, js_off = L.off_js, poly_off = L.off_poly;
     const int per_block = jumps_per_block(*ps, segs);
+    w.groups = false;
+    for (const Seg &g : segs) w.groups = w.groups || g.group > 1;
     for (size_t i = 0; i < reqs.size(); ++i) {
         const Request &r = reqs[i];
         const Seg &g = segs[i];
@@ -853,9 +871,10 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
             b.out = (uint64_t)(uintptr_t)((char *)r.d_out + out_off * 4);
             return b;
         };
-        // A wave of a stream with 32 < W < 64 is a group of one: no scan, and
-        // the outputs leave from the registers of the chain.
-        const bool alone = group_path(*ps, r, t) && group_log(ps->W[(size_t)r.stream]) == 0 &&
+        // A wave of a stream with 32 < W < 64 is a group of one (where the
+        // launch has groups): no scan, and the outputs leave from the
+        // registers of the chain.
+        const bool alone = w.groups && group_path(*ps, r, t) && group_log(ps->W[(size_t)r.stream]) == 0 &&
                            r.count < (1ull << 31);
         auto group_item = [&](int k, int n, uint64_t states, uint64_t lseg, uint64_t rec,
                               uint64_t prefix) {
@@ -1035,11 +1054,12 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
 // mode, 0 = do not overlap.  At most half the launch variant's occupancy,
 // and only where that leaves LDS for a prefix-and-jump workgroup on every
 // CU.  MTGP_OVERLAP=0 turns overlapping off; MTGP_OVERLAP=k asks for k.
-static int overlap_groups(const ParamSet &ps, const mtgp_tuning &t) {
+static int overlap_groups(const ParamSet &ps, const mtgp_tuning &t, bool groups) {
     const char *v = getenv("MTGP_OVERLAP");
     if (v && v[0] == '0') return 0;
     const int wpb = t.threads_per_stream == 64 ? t.workgroup_size / 64 : 1;
-    const int slots = variant_slots_per_cu(ps.N, t.threads_per_stream, t.outputs_per_lane, wpb);
+    const int slots = variant_slots_per_cu(ps.N, t.threads_per_stream, t.outputs_per_lane, wpb,
+                                           groups);
     const int per_cu = t.threads_per_stream == 64 ? slots / wpb : slots;
     if (per_cu < 2) return 0;
     int g = per_cu / 2;
@@ -1050,7 +1070,7 @@ static int overlap_groups(const ParamSet &ps, const mtgp_tuning &t) {
     for (int i = 0; i < nv; ++i)
         if (vi[i].tps == t.threads_per_stream && vi[i].k == t.outputs_per_lane &&
             vi[i].wpb == wpb)
-            wg_lds = vi[i].lds_bytes;
+            wg_lds = vi[i].lds_bytes[groups ? 1 : 0];
     int dev = 0, lds_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) !=
@@ -1072,7 +1092,7 @@ int run_batch(const std::shared_ptr<ParamSet> &ps, const void *d_params, uint32_
     if (allow_overlap && !w.no_alloc && !stamps) {
         hipStreamCaptureStatus cst = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s, &cst) == hipSuccess && cst == hipStreamCaptureStatusNone)
-            ov = overlap_groups(*ps, t);
+            ov = overlap_groups(*ps, t, any_groups(*ps, reqs, t));
     }
     if (ov) {
         // only a batch with both split and whole requests overlaps; for the
@@ -1152,7 +1172,7 @@ int run_batch(const std::shared_ptr<ParamSet> &ps, const void *d_params, uint32_
 
     int dev = 0;
     (void)hipGetDevice(&dev);
-    GraphKey key{d_ws, w.nA, w.nB, w.nC, w.nF, w.nCw, w.sparse,
+    GraphKey key{d_ws, w.nA, w.nB, w.nC, w.nF, w.nCw, w.sparse, w.groups,
                  w.off_A, w.off_B, w.off_C, w.off_F, w.off_pflag,
                  d_params, ps->N, t.threads_per_stream, t.outputs_per_lane, t.workgroup_size,
                  t.window_below_w, dev, stamps, per_call_errors};

@@ -74,6 +74,7 @@ struct WsState {
     // planned as sparse, whatever its own items, so that a stream's segment
     // length, and with it its cached powers, stays the same between batches
     bool shared_chip = false;
+    bool groups = false;       // the segment list holds groups
     bool overlap = false;
     int overlap_groups = 0;
     hipStream_t aux = nullptr;

@@ -112,7 +112,10 @@ struct GroupItem {
     uint64_t flag;       // 0: the request's check item raises it
     uint64_t prefix;     // outputs the prefix item makes
 };
-static_assert(sizeof(GroupItem) == sizeof(BatchItem), "GroupItem layout");
+static_assert(sizeof(GroupItem) == sizeof(BatchItem) &&
+                  offsetof(GroupItem, flag) == offsetof(BatchItem, flag) &&
+                  offsetof(GroupItem, mode) == offsetof(BatchItem, mode),
+              "GroupItem layout");
 
 // Batch workspace header (256 bytes, never part of an uploaded plan):
 //   word 0, 1   claim counters of the prefix and segment launches
@@ -184,13 +187,14 @@ struct LaunchArgs {
     uint32_t win_below;      // window path for eligible streams with W below this
     int groups_per_cu;       // persistent launches: at most this many groups per CU (0 = occupancy)
     bool persistent;
+    bool groups;             // launch_variant: items may carry MODE_GROUP
     int num_cus;
     void *stream;
 };
 
 struct VariantInfo {
     int tps, k, wpb;
-    size_t lds_bytes;
+    size_t lds_bytes[2];     // per workgroup, without and with room for groups
 };
 
 int variant_count(int n_words, VariantInfo *out, int max_out);
@@ -222,7 +226,7 @@ constexpr bool has_wide(int N) { return N > (int)WIDE_MIN_W; }
 hipError_t launch_sparse(int n_words, const LaunchArgs &a, uint32_t n_wide,
                          uint32_t *wide_counter);
 hipError_t launch_check(int n_words, const LaunchArgs &a);
-int variant_slots_per_cu(int n_words, int tps, int k, int wpb);
+int variant_slots_per_cu(int n_words, int tps, int k, int wpb, bool groups);
 hipError_t launch_seed(const uint32_t *params, uint32_t *states, uint32_t stride,
                        uint32_t n_streams, hipStream_t s);
 hipError_t launch_reset(uint32_t *counter, hipStream_t s);

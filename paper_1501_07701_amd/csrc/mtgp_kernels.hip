@@ -99,7 +99,11 @@ __host__ __device__ constexpr int buf_words(int N, int SMAX, int TPS) {
     return ((TPS == 64 ? N : 2 * N) + 4 * SMAX + 63) / 64 * 64;
 }
 
-template <int N, int TPS, int K>
+// GRP: with room for groups (segment launches of batches that have them; a
+// group takes nearly twice the LDS of the other paths, so launches that run
+// none keep the smaller block: 16,000 mexp-3217 streams of 3,000 outputs
+// 127 us against 167).
+template <int N, int TPS, int K, bool GRP = false>
 struct Core {
     static constexpr int SMAX = TPS * K;
     static constexpr int BUF = buf_words(N, SMAX, TPS);
@@ -115,7 +119,8 @@ struct Core {
     static constexpr int WLDS = (N + WNMAX + 63) / 64 * 64 + WTAIL;
     // Group path: the members' buffers (eight of a state and two windows, or
     // fewer longer ones), the tables and the scan matrices.
-    static constexpr bool GROUPS = TPS == 64 && has_groups(N);
+    static constexpr bool GROUPS = GRP;
+    static_assert(!GRP || (TPS == 64 && has_groups(N)), "groups: one wave, a short state");
     static constexpr int GTAIL = 32 + GROUP_ROUNDS * WIN_MAT_WORDS;
     static constexpr int GLDS = GROUPS ? 8 * (N + 2 * 64) + GTAIL : 0;
     static constexpr int WIDE_LDS = (BUF + 32) > WLDS ? (BUF + 32) : WLDS;
@@ -841,10 +846,10 @@ struct Core {
             steps_group<F32, GROUP_E, true>(p, item, buf, lg, q, p.W * q * GROUP_E, lane, fail);
             return;
         }
-        switch ((N - 1) / p.W) {  // whole windows of E W words
+        switch ((N - 1) / p.W) {  // whole windows of E W words, W <= 32 and N > 96
 #define MTGP_GE(E) \
     case E: steps_group<F32, E, false>(p, item, buf, lg, 1u, p.W * E, lane, fail); break;
-            MTGP_GE(1) MTGP_GE(2) MTGP_GE(3) MTGP_GE(4) MTGP_GE(5) MTGP_GE(6) MTGP_GE(7)
+            MTGP_GE(3) MTGP_GE(4) MTGP_GE(5) MTGP_GE(6) MTGP_GE(7)
 #undef MTGP_GE
             default: steps_group<F32, 8, false>(p, item, buf, lg, 1u, p.W * 8, lane, fail); break;
         }
@@ -953,12 +958,12 @@ __device__ __forceinline__ uint32_t group_first(uint32_t v, uint32_t *slot) {
 
 // The work loop shared by the generation kernels: claim an item (or take
 // stream `it` in plain mode), run it, raise its completion flag.
-template <int N, int TPS, int K, int WPB, bool RAW, bool LAT>
+template <int N, int TPS, int K, int WPB, bool RAW, bool LAT, bool GRP>
 __device__ __forceinline__ void gen_body(const uint32_t *__restrict__ params,
                                          const BatchItem *__restrict__ items, uint32_t n_items,
                                          uint32_t *__restrict__ counter, uint32_t persistent,
                                          uint32_t win_below, PlainArgs plain) {
-    using C = Core<N, TPS, K>;
+    using C = Core<N, TPS, K, GRP>;
     extern __shared__ uint32_t lds[];
     __shared__ uint32_t s_claim;
     const uint32_t wave =
@@ -987,8 +992,8 @@ __device__ __forceinline__ void gen_body(const uint32_t *__restrict__ params,
             item.state_in = item.state_out = (uint64_t)(uintptr_t)row;
             item.raw = item.verify = item.rec = item.flag = 0;
         }
-        if (C::GROUPS && !RAW && !LAT && (item.mode & MODE_GROUP)) {
-            if constexpr (C::GROUPS && !RAW && !LAT) {
+        if (GRP && (item.mode & MODE_GROUP)) {
+            if constexpr (GRP) {
                 const GroupItem g = *reinterpret_cast<const GroupItem *>(items + it);
                 const uint32_t *prm = params + (uint64_t)g.stream * P_WORDS;
                 if (g.mode & MODE_F32) C::template run_group<true>(prm, g, buf, lane);
@@ -1019,14 +1024,15 @@ __device__ __forceinline__ void gen_body(const uint32_t *__restrict__ params,
     }
 }
 
-// Segments of a batch, whole unsplit requests and plain calls.
-template <int N, int TPS, int K, int WPB>
+// Segments of a batch, whole unsplit requests and plain calls; GRP: groups
+// among them.
+template <int N, int TPS, int K, int WPB, bool GRP>
 __global__ void __launch_bounds__(TPS == 64 ? 64 * WPB : TPS)
 gen_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__ items,
            uint32_t n_items, uint32_t *__restrict__ counter, uint32_t persistent,
            uint32_t win_below, PlainArgs plain) {
-    gen_body<N, TPS, K, WPB, false, false>(params, items, n_items, counter, persistent,
-                                           win_below, plain);
+    gen_body<N, TPS, K, WPB, false, false, GRP>(params, items, n_items, counter, persistent,
+                                                win_below, plain);
 }
 
 // Plain calls of few streams: one wave per stream with room for longer runs
@@ -1036,8 +1042,8 @@ __global__ void __launch_bounds__(256)
 few_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__ items,
            uint32_t n_items, uint32_t *__restrict__ counter, uint32_t persistent,
            uint32_t win_below, PlainArgs plain) {
-    gen_body<N, 64, 8, 4, false, true>(params, items, n_items, counter, persistent, win_below,
-                                       plain);
+    gen_body<N, 64, 8, 4, false, true, false>(params, items, n_items, counter, persistent,
+                                              win_below, plain);
 }
 
 // Segments and whole requests of a batch with fewer items than the chip has
@@ -1124,8 +1130,8 @@ __global__ void __launch_bounds__(256)
 prefix_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__ items,
               uint32_t n_items, uint32_t *__restrict__ counter, uint32_t persistent,
               uint32_t win_below, PlainArgs plain) {
-    gen_body<N, 64, prefix_k(N), 4, true, true>(params, items, n_items, counter, persistent,
-                                                win_below, plain);
+    gen_body<N, 64, prefix_k(N), 4, true, true, false>(params, items, n_items, counter,
+                                                       persistent, win_below, plain);
 }
 
 // Request checks of split requests (MODE_FIXUP items), after every segment
@@ -1680,9 +1686,9 @@ typedef void (*GenFn)(const uint32_t *, const BatchItem *, uint32_t, uint32_t *,
 // Launches one of the generation kernels with the LDS of Core<N, TPS, K>
 // times the groups per workgroup; persistent launches fill every CU to its
 // occupancy with no more groups than items.
-template <int N, int TPS, int K, int WPB>
+template <int N, int TPS, int K, int WPB, bool GRP = false>
 static hipError_t launch_with(GenFn fn, bool *attr_set, const LaunchArgs &a) {
-    using C = Core<N, TPS, K>;
+    using C = Core<N, TPS, K, GRP>;
     const int threads = TPS == 64 ? 64 * WPB : TPS;
     const size_t lds = (size_t)C::LDS_WORDS * 4 * (TPS == 64 ? WPB : 1);
     if (!*attr_set) {  // benign race: idempotent attribute
@@ -1710,10 +1716,10 @@ static hipError_t launch_with(GenFn fn, bool *attr_set, const LaunchArgs &a) {
     return hipGetLastError();
 }
 
-template <int N, int TPS, int K, int WPB>
+template <int N, int TPS, int K, int WPB, bool GRP>
 static hipError_t launch_gen(const LaunchArgs &a) {
     static bool attr_set = false;
-    return launch_with<N, TPS, K, WPB>(gen_kernel<N, TPS, K, WPB>, &attr_set, a);
+    return launch_with<N, TPS, K, WPB, GRP>(gen_kernel<N, TPS, K, WPB, GRP>, &attr_set, a);
 }
 
 template <int N>
@@ -1812,37 +1818,43 @@ hipError_t launch_check(int n_words, const LaunchArgs &a) {
     }
 }
 
-template <int N, int TPS, int K, int WPB>
+template <int N, int TPS, int K, int WPB, bool GRP>
 static size_t lds_bytes_of() {
-    return (size_t)Core<N, TPS, K>::LDS_WORDS * 4 * (TPS == 64 ? WPB : 1);
+    return (size_t)Core<N, TPS, K, GRP>::LDS_WORDS * 4 * (TPS == 64 ? WPB : 1);
 }
 
 // Streams a CU runs at once with this variant (waves for TPS = 64, else
 // workgroups), from the occupancy the runtime reports; 0 on error.
-template <int N, int TPS, int K, int WPB>
+template <int N, int TPS, int K, int WPB, bool GRP>
 static int slots_of() {
     static int cached = -1;  // benign race: idempotent query
     if (cached < 0) {
         int per_cu = 0;
         const int threads = TPS == 64 ? 64 * WPB : TPS;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, gen_kernel<N, TPS, K, WPB>,
-                                                         threads, lds_bytes_of<N, TPS, K, WPB>()) !=
-            hipSuccess)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &per_cu, gen_kernel<N, TPS, K, WPB, GRP>, threads,
+                lds_bytes_of<N, TPS, K, WPB, GRP>()) != hipSuccess)
             return 0;
         cached = per_cu * (TPS == 64 ? WPB : 1);
     }
     return cached;
 }
 
+// A launch variant: [0] without groups, [1] with (the same where there are
+// none).
 struct Variant {
     int N, tps, k, wpb;
-    hipError_t (*launch)(const LaunchArgs &);
-    size_t (*lds)();
-    int (*slots)();
+    hipError_t (*launch[2])(const LaunchArgs &);
+    size_t (*lds[2])();
+    int (*slots[2])();
 };
 
-#define MTGP_V(N, T, K, P) \
-    {N, T, K, P, &launch_gen<N, T, K, P>, &lds_bytes_of<N, T, K, P>, &slots_of<N, T, K, P>}
+#define MTGP_G(N, T) ((T) == 64 && has_groups(N))
+#define MTGP_V(N, T, K, P)                                                              \
+    {N, T, K, P,                                                                        \
+     {&launch_gen<N, T, K, P, false>, &launch_gen<N, T, K, P, MTGP_G(N, T)>},           \
+     {&lds_bytes_of<N, T, K, P, false>, &lds_bytes_of<N, T, K, P, MTGP_G(N, T)>},       \
+     {&slots_of<N, T, K, P, false>, &slots_of<N, T, K, P, MTGP_G(N, T)>}}
 #define MTGP_VARIANTS(N)                                                              \
     MTGP_V(N, 64, 1, 4), MTGP_V(N, 64, 2, 4), MTGP_V(N, 64, 4, 4), MTGP_V(N, 64, 8, 4), \
     MTGP_V(N, 64, 2, 8), MTGP_V(N, 64, 4, 8), MTGP_V(N, 64, 4, 16),                   \
@@ -1856,15 +1868,17 @@ static const Variant kVariants[] = {
 // LDS per workgroup on gfx950.
 static constexpr size_t kLdsBytes = 160 * 1024;
 
+static bool fits(const Variant &v) { return v.lds[1]() + 64 <= kLdsBytes; }
+
 int variant_count(int n_words, VariantInfo *out, int max_out) {
     int c = 0;
     for (const Variant &v : kVariants) {
-        if (v.N != n_words || v.lds() + 64 > kLdsBytes) continue;
+        if (v.N != n_words || !fits(v)) continue;
         if (out && c < max_out) {
             out[c].tps = v.tps;
             out[c].k = v.k;
             out[c].wpb = v.wpb;
-            out[c].lds_bytes = v.lds();
+            for (int g = 0; g < 2; ++g) out[c].lds_bytes[g] = v.lds[g]();
         }
         ++c;
     }
@@ -1874,21 +1888,19 @@ int variant_count(int n_words, VariantInfo *out, int max_out) {
 hipError_t launch_variant(int n_words, int tps, int k, int wpb, const LaunchArgs &a,
                           bool *found) {
     for (const Variant &v : kVariants) {
-        if (v.N == n_words && v.tps == tps && v.k == k && v.wpb == wpb &&
-            v.lds() + 64 <= kLdsBytes) {
+        if (v.N == n_words && v.tps == tps && v.k == k && v.wpb == wpb && fits(v)) {
             *found = true;
-            return v.launch(a);
+            return v.launch[a.groups ? 1 : 0](a);
         }
     }
     *found = false;
     return hipSuccess;
 }
 
-int variant_slots_per_cu(int n_words, int tps, int k, int wpb) {
+int variant_slots_per_cu(int n_words, int tps, int k, int wpb, bool groups) {
     for (const Variant &v : kVariants)
-        if (v.N == n_words && v.tps == tps && v.k == k && v.wpb == wpb &&
-            v.lds() + 64 <= kLdsBytes)
-            return v.slots();
+        if (v.N == n_words && v.tps == tps && v.k == k && v.wpb == wpb && fits(v))
+            return v.slots[groups ? 1 : 0]();
     return 0;
 }
 
