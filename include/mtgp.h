@@ -260,7 +260,12 @@ typedef struct mtgp_tuning {
                                a batch splits the streams that need more
                                steps than max(this, a multiple (0.75 to
                                1) of its total steps over the streams
-                               the device runs at once) */
+                               the device runs at once); a batch of
+                               mexp 3217 cuts streams with a linear rec_tbl
+                               and W below window_below_w once they need more
+                               steps than this, into segments of at least
+                               max(8192, this * max(8, W / 2)) outputs,
+                               several of which run on one wave */
     int window_below_w;     /* with threads_per_stream = 64, streams with a
                                linear rec_tbl and step width W = N - pos below
                                this (at most 64) run the windowed scan instead

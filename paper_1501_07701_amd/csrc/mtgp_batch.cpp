@@ -371,22 +371,21 @@ size_t batch_min_ws_bytes(int n_items) {
     return HDR_BYTES + al256((size_t)std::max(n_items, 0) * sizeof(BatchItem));
 }
 
-// Segments of a request that would run together on one wave: as many as its
-// step width allows (group_members), fewer for short requests, 1 = no group.
-// A member pays a jump, about the time of 4,000 outputs at N = 101, so it
-// gets at least 16,384.
+// Whether a stream's segments may run as a group.
 static bool group_path(const ParamSet &ps, const Request &r, const mtgp_tuning &t) {
     return has_groups(ps.N) && t.threads_per_stream == 64 && ps.lin[(size_t)r.stream] &&
            ps.W[(size_t)r.stream] < (uint32_t)t.window_below_w;
 }
 
+// Segments of a request that run together on one wave, 1 = no group.  A
+// request that the tuning's floor of dependent steps leaves whole is not
+// grouped: its stream then needs no polynomial (a first call of 1000 requests
+// of 2^14 .. 2^16 outputs takes 5 ms; 38 where they are cut).
 static int group_size(const ParamSet &ps, const Request &r, const mtgp_tuning &t) {
-    if (!group_path(ps, r, t)) return 1;
     const uint32_t W = ps.W[(size_t)r.stream];
-    int n = group_members(W);
-    // (a group of W > 32 is whole: its rows are compiled for all members)
-    while (n > 1 && r.count < (uint64_t)n * 16384u) n = W > 32 ? 1 : n / 2;
-    return n;
+    if (!group_path(ps, r, t) || !group_long_enough(W, r.count, t.jump_target_steps)) return 1;
+    const uint64_t so = step_outputs(ps, r.stream, t);
+    return (r.count + so - 1) / so > (uint64_t)t.jump_target_steps ? group_members(W) : 1;
 }
 
 // Whether any request of a batch is long enough to run in groups.
@@ -445,24 +444,6 @@ static bool is_sparse(const ParamSet &ps, const std::vector<Request> &reqs, uint
     return items <= (uint64_t)std::max(1, device_cus()) * SPARSE_ITEMS_PER_CU;
 }
 
-// Segment length for a target of v outputs: v rounded down to m * 2^e with
-// m in {4, 5, 6, 7} (at most 20% short), at least 256.  The coarse grid
-// keeps a stream's segment length, and so its cached jump polynomials, the
-// same from batch to batch when the target moves a little; whole 256-word
-// multiples keep every segment's stores line-aligned.
-static uint64_t segment_length(uint64_t v) {
-    if (v < 1024) return std::max<uint64_t>(256, v / 256 * 256);
-    const int e = 63 - __builtin_clzll(v) - 2;  // v / 2^e in [4, 8), e >= 8
-    return (v >> e) << e;
-}
-
-// Length of a group's segments for at least v outputs each: v rounded up to
-// m * 2^e, m in 16 .. 31 (at most 6% long), for the same reasons.
-static uint64_t group_length(uint64_t v) {
-    const int e = std::max(0, 63 - __builtin_clzll(v | 1) - 4);
-    return ((v + (1ull << e) - 1) >> e) << e;
-}
-
 // Splits a request when it needs more than T dependent steps, for a stream
 // polynomial of degree D (D < 1: never).  With `groups`, requests of narrow
 // streams are cut further, into whole groups.
@@ -475,8 +456,8 @@ static void decide(const ParamSet &ps, const Request &r, int D, uint64_t T, cons
     const uint64_t so = step_outputs(ps, r.stream, t, sparse);
     const int n = groups ? group_size(ps, r, t) : 1;
     if (n > 1) {
-        const uint64_t items = std::max<uint64_t>(1, (r.count + so * T - 1) / (so * T));
-        const uint64_t lseg = group_length((r.count + items * n - 1) / (items * n));
+        const uint64_t lseg =
+            group_length(ps.W[(size_t)r.stream], r.count, so * T, t.jump_target_steps);
         if (lseg > (uint64_t)D + 1 && lseg < (1ull << 31) && r.count > lseg) {
             g.C = (int)((r.count + lseg - 1) / lseg);
             g.lseg = lseg;

@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "mtgp_split.hpp"
+
 namespace mtgp {
 
 // Device parameter block: 1024 words (4 KB) per stream.
@@ -35,16 +37,9 @@ constexpr int WIN_EMAX = 8;
 constexpr int WIN_MAXROUNDS = 5;
 constexpr int WIN_MAT_WORDS = 128;   // 8 nibbles x 16 entries
 
-// Groups: several segments of one narrow stream run together on one wave,
-// where a whole wave's window of a short state would be cut into tiny chunks
-// per residue class.  W <= 32: 2^group_log(W) segments, each on
-// 64 >> group_log(W) lanes; W > 32: every lane takes its class of each of
-// GROUP_ROWS segments.  Only for N <= 128 (several states fit a wave's LDS)
+// Groups (mtgp_split.hpp) only for N <= 128 (several states fit a wave's LDS)
 // and linear recursion tables.
 constexpr bool has_groups(int N) { return N <= 128; }
-constexpr int group_log(uint32_t W) { return W <= 8 ? 3 : W <= 16 ? 2 : W <= 32 ? 1 : 0; }
-constexpr int GROUP_ROWS = 4;
-constexpr int group_members(uint32_t W) { return W <= 32 ? 1 << group_log(W) : GROUP_ROWS; }
 constexpr int GROUP_E = 8;           // most elements per lane and window
 constexpr int GROUP_ROUNDS = 2;      // scan rounds (W = 2: four lanes per class)
 
