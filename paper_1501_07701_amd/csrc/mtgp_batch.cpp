@@ -388,10 +388,11 @@ static int group_size(const ParamSet &ps, const Request &r, const mtgp_tuning &t
     return (r.count + so - 1) / so > (uint64_t)t.jump_target_steps ? group_members(W) : 1;
 }
 
-// Whether any request of a batch is long enough to run in groups.
+// Whether any request of a batch is long enough to run in groups; never where
+// several batches share the chip (WsState::shared_chip).
 static bool any_groups(const ParamSet &ps, const std::vector<Request> &reqs,
-                       const mtgp_tuning &t) {
-    if (!has_groups(ps.N)) return false;
+                       const mtgp_tuning &t, bool shared_chip) {
+    if (!has_groups(ps.N) || shared_chip) return false;
     for (const Request &r : reqs)
         if (group_size(ps, r, t) > 1) return true;
     return false;
@@ -403,7 +404,7 @@ static bool any_groups(const ParamSet &ps, const std::vector<Request> &reqs,
 // so that only streams on the critical path are cut and each segment is
 // short against the whole launch.
 static uint64_t effective_target(const ParamSet &ps, const std::vector<Request> &reqs,
-                                 const mtgp_tuning &t) {
+                                 const mtgp_tuning &t, bool groups) {
     if (t.jump_target_steps <= 0) return 0;
     uint64_t total = 0;
     for (const Request &r : reqs) {
@@ -412,7 +413,7 @@ static uint64_t effective_target(const ParamSet &ps, const std::vector<Request> 
     }
     const int wpb = t.threads_per_stream == 64 ? t.workgroup_size / 64 : 1;
     const int per_cu = variant_slots_per_cu(ps.N, t.threads_per_stream, t.outputs_per_lane, wpb,
-                                            any_groups(ps, reqs, t));
+                                            groups);
     const uint64_t slots = (uint64_t)std::max(1, per_cu) * (uint64_t)std::max(1, device_cus());
     // a multiple of the balanced share of steps per resident stream: more,
     // shorter segments shorten the tail of the segment phase but every
@@ -480,10 +481,10 @@ static void decide(const ParamSet &ps, const Request &r, int D, uint64_t T, cons
 }
 
 static bool wants_split(const ParamSet &ps, const Request &r, uint64_t T, const mtgp_tuning &t,
-                        bool sparse) {
+                        bool groups, bool sparse) {
     if (!T) return false;
     const uint64_t so = step_outputs(ps, r.stream, t, sparse);
-    return ((r.count + so - 1) / so > T || group_size(ps, r, t) > 1) &&
+    return ((r.count + so - 1) / so > T || (groups && group_size(ps, r, t) > 1)) &&
            r.count > (uint64_t)ps.mexp + 128;
 }
 
@@ -755,11 +756,12 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
     const int N = ps->N;
     std::vector<Seg> segs(reqs.size());
     std::vector<int> want;
-    uint64_t T = effective_target(*ps, reqs, t);
+    bool groups = any_groups(*ps, reqs, t, w.shared_chip);
+    uint64_t T = effective_target(*ps, reqs, t, groups);
     const bool sparse = !w.shared_chip && is_sparse(*ps, reqs, T, t);
     for (size_t i = 0; i < reqs.size(); ++i) {
         segs[i].req = (int)i;
-        if (wants_split(*ps, reqs[i], T, t, sparse)) want.push_back(reqs[i].stream);
+        if (wants_split(*ps, reqs[i], T, t, groups, sparse)) want.push_back(reqs[i].stream);
     }
     if (!want.empty() && !w.no_alloc) {
         int rc = ensure_jumps(ps, d_params, d_states, stride, want, t, s);
@@ -776,9 +778,9 @@ static int build_plan(const std::shared_ptr<ParamSet> &ps, const void *d_params,
                 if (!(w.no_alloc && ps->dirty[(size_t)reqs[i].stream]))
                     sjs[i] = ps->jumps[reqs[i].stream];
     }
-    // plan, doubling the target until the workspace fits
+    // plan, giving up the groups and then doubling the target until the
+    // workspace fits
     Layout L;
-    bool groups = true;  // given up first where the workspace is small
     while (true) {
         for (size_t i = 0; i < reqs.size(); ++i) {
             const int D = (sjs[i] && sjs[i]->status == 1) ? sjs[i]->D : 0;
@@ -1073,17 +1075,18 @@ int run_batch(const std::shared_ptr<ParamSet> &ps, const void *d_params, uint32_
     if (allow_overlap && !w.no_alloc && !stamps) {
         hipStreamCaptureStatus cst = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s, &cst) == hipSuccess && cst == hipStreamCaptureStatusNone)
-            ov = overlap_groups(*ps, t, any_groups(*ps, reqs, t));
+            ov = overlap_groups(*ps, t, any_groups(*ps, reqs, t, w.shared_chip));
     }
     if (ov) {
         // only a batch with both split and whole requests overlaps; for the
         // others the plan is the same either way, and phase-timed calls keep
         // using the cached one
-        const uint64_t T = effective_target(*ps, reqs, t);
+        const bool groups = any_groups(*ps, reqs, t, w.shared_chip);
+        const uint64_t T = effective_target(*ps, reqs, t, groups);
         bool any_split = false, any_whole = false;
-        const bool sparse = is_sparse(*ps, reqs, T, t);
+        const bool sparse = !w.shared_chip && is_sparse(*ps, reqs, T, t);
         for (const Request &r : reqs)
-            (wants_split(*ps, r, T, t, sparse) ? any_split : any_whole) = true;
+            (wants_split(*ps, r, T, t, groups, sparse) ? any_split : any_whole) = true;
         if (!(any_split && any_whole)) ov = 0;
     }
     if (ov && !w.aux) {
@@ -1294,10 +1297,11 @@ int mtgp_batch_workspace_query(const void *d_params, const mtgp_work *h_items, i
     const mtgp_tuning t = tuning_for(ps->N);
     std::vector<int> want;
     std::vector<Request> reqs = to_requests(h_items, n_items);
-    const uint64_t T = effective_target(*ps, reqs, t);
+    const bool groups = any_groups(*ps, reqs, t, false);
+    const uint64_t T = effective_target(*ps, reqs, t, groups);
     const bool sparse = is_sparse(*ps, reqs, T, t);
     for (const Request &r : reqs)
-        if (wants_split(*ps, r, T, t, sparse)) want.push_back(r.stream);
+        if (wants_split(*ps, r, T, t, groups, sparse)) want.push_back(r.stream);
     if (!want.empty()) {
         rc = ensure_jumps(ps, d_params, nullptr, 0, want, t, nullptr);
         if (rc) return rc;
@@ -1311,12 +1315,12 @@ int mtgp_batch_workspace_query(const void *d_params, const mtgp_work *h_items, i
             const StreamJump *sj = ps->jumps[(size_t)k].get();
             segs[i].req = (int)i;
             if (sj && sj->status == 1 && !ps->dirty[(size_t)k]) {
-                decide(*ps, reqs[i], sj->D, T, t, true, sparse, segs[i]);
+                decide(*ps, reqs[i], sj->D, T, t, groups, sparse, segs[i]);
             } else if (!sj || ps->dirty[(size_t)k]) {
                 // the polynomial will be built from the stream's state at
                 // generation time: size for the most segments (D = 1) and
                 // the largest degree (mexp)
-                decide(*ps, reqs[i], 1, T, t, true, sparse, segs[i]);
+                decide(*ps, reqs[i], 1, T, t, groups, sparse, segs[i]);
                 if (segs[i].C > 1) segs[i].Dsize = (int)ps->mexp;
             }
         }

@@ -72,7 +72,9 @@ struct WsState {
     uint32_t nCw = 0;
     // several batches share the chip (the server's slots): no batch is
     // planned as sparse, whatever its own items, so that a stream's segment
-    // length, and with it its cached powers, stays the same between batches
+    // length, and with it its cached powers, stays the same between batches;
+    // nor in groups, whose powers each new stream and length pays for inside
+    // a request
     bool shared_chip = false;
     bool groups = false;       // the segment list holds groups
     bool overlap = false;
