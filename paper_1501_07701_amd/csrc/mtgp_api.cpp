@@ -276,6 +276,12 @@ mtgp_tuning tuning_for(int N) {
     return it == g_tune.end() ? default_tuning(N) : it->second;
 }
 
+bool default_launch(int N, const mtgp_tuning &t) {
+    const mtgp_tuning d = default_tuning(N);
+    return t.threads_per_stream == d.threads_per_stream &&
+           t.outputs_per_lane == d.outputs_per_lane && t.workgroup_size == d.workgroup_size;
+}
+
 static int wpb_of(const mtgp_tuning &t) {
     return t.threads_per_stream == 64 ? t.workgroup_size / 64 : 1;
 }
@@ -319,8 +325,9 @@ static int generate_plain(const void *d_params, uint32_t *d_states, int stride, 
     // fill the chip, so the dependent chain sets the time.  1024 mexp-44497
     // streams of 12,289 words 65 us (75 by the batch kernel), 100 mexp-11213
     // streams of 20,000 101 (113); 4096 mexp-3217 streams of 3,000 64 (61).
+    // A launch that the caller chose runs as it was chosen.
     const int few = ps->N > 400 ? 16 : 8;
-    if (t.threads_per_stream == 64 && n_streams <= few * a.num_cus) {
+    if (default_launch(ps->N, t) && n_streams <= few * a.num_cus) {
         a.win_below = (uint32_t)t.window_below_w;
         const hipError_t e = launch_few(ps->N, a);
         return e == hipSuccess ? MTGP_OK : hip_fail(e, "kernel launch");

@@ -436,7 +436,7 @@ constexpr uint64_t SPARSE_ITEMS_PER_CU = 6;
 // cut as at N = 351).  From three items per CU to fourteen it times alike.
 static bool is_sparse(const ParamSet &ps, const std::vector<Request> &reqs, uint64_t T,
                       const mtgp_tuning &t) {
-    if (!has_wide(ps.N) || t.threads_per_stream != 64) return false;
+    if (!has_wide(ps.N) || !default_launch(ps.N, t)) return false;
     uint64_t items = 0;
     for (const Request &r : reqs) {
         const uint64_t so = step_outputs(ps, r.stream, t);

@@ -98,6 +98,10 @@ int device_cus();
 int words_for_mexp(uint32_t mexp);
 std::shared_ptr<ParamSet> lookup_params(const void *d_params, int n_streams);
 mtgp_tuning tuning_for(int N);
+// Whether a tuning's launch (threads per stream, outputs per lane, workgroup)
+// is the default one: the library then runs few streams and batches of few
+// items by kernels made for them.  Any other launch is run as it was asked for.
+bool default_launch(int N, const mtgp_tuning &t);
 int launch_tuned(int N, const mtgp_tuning &t, const LaunchArgs &a);
 
 // Outputs per step the generator achieves for step width W under a tuning;
