@@ -439,6 +439,7 @@ static bool is_sparse(const ParamSet &ps, const std::vector<Request> &reqs, uint
     if (!has_wide(ps.N) || !default_launch(ps.N, t)) return false;
     uint64_t items = 0;
     for (const Request &r : reqs) {
+        if (r.flag) return false;  // sparse_kernel raises no completion flags
         const uint64_t so = step_outputs(ps, r.stream, t);
         items += T ? std::max<uint64_t>(1, (r.count + so * T - 1) / (so * T)) : 1;
     }

@@ -1051,7 +1051,8 @@ few_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__ it
 // its rows (four rows of 64 outputs 980 cycles, of which some 300 are the
 // chain), so streams of wide steps are run by whole workgroups, a row or a
 // few per wave.  The workgroups first claim the wide items, then their waves
-// the others.
+// the others.  No completion flags: requests that carry one are the server's,
+// whose batches are never sparse.
 constexpr int wide_k(int N) { return N <= 400 ? 1 : N <= 800 ? 2 : 4; }
 
 template <int N>
@@ -1083,14 +1084,6 @@ sparse_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__
             B::template run<true, false, false>(prm, item, lds, threadIdx.x, fail, 0u);
         else
             B::template run<false, false, false>(prm, item, lds, threadIdx.x, fail, 0u);
-        if (item.flag != 0) {
-            // publish completion to the host, after every thread's stores
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
-            __syncthreads();
-            if (threadIdx.x == 0)
-                __hip_atomic_store(reinterpret_cast<uint32_t *>(item.flag), 1u, __ATOMIC_RELEASE,
-                                   __HIP_MEMORY_SCOPE_SYSTEM);
-        }
     }
     __syncthreads();
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1109,14 +1102,6 @@ sparse_kernel(const uint32_t *__restrict__ params, const BatchItem *__restrict__
             A::template run<true, false, true>(prm, item, buf, lane, fail, win_below);
         else
             A::template run<false, false, true>(prm, item, buf, lane, fail, win_below);
-        if (item.flag != 0) {
-            // every lane stores the flag: with a store by lane 0 alone the
-            // compiler splits the claim loop by lane
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
-            group_sync<64>();
-            __hip_atomic_store(reinterpret_cast<uint32_t *>(item.flag), 1u, __ATOMIC_RELEASE,
-                               __HIP_MEMORY_SCOPE_SYSTEM);
-        }
     }
 }
 
