@@ -121,6 +121,16 @@ static void parallel_for(int n, F f) {
     for (auto &x : th) x.join();
 }
 
+// Cost model: outputs a stream yields per dependent step of the wide path
+// (one LDS round trip).  Narrow streams with a linear rec_tbl run the
+// windowed scan instead: about 60 + W outputs per wide-step time on a full
+// chip, fewer by a wave alone, where the scan's instructions set its time.
+// There 40 is ahead of 64 at N = 351 (100 x 10^6 outputs 505 us against 584,
+// 60 streams of 2^18 405 against 463, six such batches 12 % in the mean) and
+// at N = 726 (700 against 698, 482 against 509, six batches 2.1 %); at N =
+// 1391 64 (1040 against 1038, 732 against 709, but 48 x 2^22 1133 against
+// 1183 and 512 x 2^10 .. 2^22 1493 against 1543: jumps are dear).  60 + W is
+// behind both throughout, by 2 to 25 %.
 uint64_t step_outputs(const ParamSet &ps, int stream, const mtgp_tuning &t, bool sparse) {
     const uint32_t W = ps.W[(size_t)stream];
     const uint64_t smax = (uint64_t)t.threads_per_stream * (uint64_t)t.outputs_per_lane;
@@ -128,7 +138,7 @@ uint64_t step_outputs(const ParamSet &ps, int stream, const mtgp_tuning &t, bool
     if (W >= 64) s = W & ~31u;
     else if (t.threads_per_stream == 64 && ps.lin[(size_t)stream] &&
              W < (uint32_t)t.window_below_w)
-        s = !sparse ? 60 + W : ps.N <= 400 ? 40 : 64;
+        s = !sparse ? 60 + W : ps.N <= 800 ? 40 : 64;
     else s = W;
     return std::max<uint64_t>(1, std::min(s, smax));
 }
@@ -430,10 +440,10 @@ constexpr uint64_t SPARSE_ITEMS_PER_CU = 6;
 // A batch whose work items (at the full chip's rates) are too few to fill
 // the chip: up to one and a half per SIMD, so that waves are mostly alone.
 // Its segment launch runs wide streams by whole workgroups, and its narrow
-// streams are cut by the rate of a wave alone: 100 mexp-11213 streams of 10^6
-// outputs 503 us (678 by the batch kernel; 605 with the narrow streams cut as
-// on a full chip), 512 mexp-44497 streams of 2^10 .. 2^22 1490 (1590; 1565
-// cut as at N = 351).  From three items per CU to fourteen it times alike.
+// streams are cut by the rate of a wave alone (step_outputs): 100 mexp-11213
+// streams of 10^6 outputs 503 us (678 by the batch kernel), 512 mexp-44497
+// streams of 2^10 .. 2^22 1490 (1590).  From three items per CU to fourteen
+// it times alike.
 static bool is_sparse(const ParamSet &ps, const std::vector<Request> &reqs, uint64_t T,
                       const mtgp_tuning &t) {
     if (!has_wide(ps.N) || !default_launch(ps.N, t)) return false;
