@@ -252,9 +252,10 @@ int mtgp_batch_errors(void *d_workspace, void *stream, uint32_t *n);
  * several streams per workgroup; 256/512/1024 = one stream per workgroup),
  * outputs per lane per step, and workgroup size.  The default launch (its
  * three values) stands for the library's choice: calls that leave the chip
- * nearly empty (plain calls of at most 8 streams per CU, 16 from mexp 23209
- * on; batches of at most 6 segments per CU from mexp 11213 on) then run by
- * kernels made for them.  Any other launch is used for calls of all sizes. */
+ * nearly empty (plain calls of at most 6 streams per CU at mexp 3217, 8 at
+ * 11213, 16 above; batches of at most 6 segments per CU from mexp 11213 on)
+ * then run by kernels made for them.  Any other launch is used for calls of
+ * all sizes. */
 typedef struct mtgp_tuning {
     int threads_per_stream;
     int outputs_per_lane;

@@ -321,12 +321,13 @@ static int generate_plain(const void *d_params, uint32_t *d_states, int stride, 
     a.persistent = false;
     a.num_cus = device_cus();
     a.stream = s;
-    // Few streams: two waves per SIMD (four where the state is long) do not
-    // fill the chip, so the dependent chain sets the time.  1024 mexp-44497
-    // streams of 12,289 words 65 us (75 by the batch kernel), 100 mexp-11213
-    // streams of 20,000 101 (113); 4096 mexp-3217 streams of 3,000 64 (61).
-    // A launch that the caller chose runs as it was chosen.
-    const int few = ps->N > 400 ? 16 : 8;
+    // Few streams: up to two waves per SIMD (one and a half where the state
+    // is short, four where it is long) do not fill the chip, so the dependent
+    // chain sets the time.  By this kernel and by the batch kernel, u32 of
+    // 20,000 each: mexp 3217, 1000 streams 282 us (286), 2000 300 (295); 11213,
+    // 2000 136 (140), 4096 streams alike; 23209, 4000 161 (175); 44497, 4000
+    // 183 (200).  A launch that the caller chose runs as it was chosen.
+    const int few = ps->N > 400 ? 16 : ps->N > 128 ? 8 : 6;
     if (default_launch(ps->N, t) && n_streams <= few * a.num_cus) {
         a.win_below = (uint32_t)t.window_below_w;
         const hipError_t e = launch_few(ps->N, a);
