@@ -469,7 +469,8 @@ static void decide(const ParamSet &ps, const Request &r, int D, uint64_t T, cons
     const int n = groups ? group_size(ps, r, t) : 1;
     if (n > 1) {
         const uint64_t lseg =
-            group_length(ps.W[(size_t)r.stream], r.count, so * T, t.jump_target_steps);
+            group_length(ps.W[(size_t)r.stream], r.count, segment_length(so * T),
+                         t.jump_target_steps);
         if (lseg > (uint64_t)D + 1 && lseg < (1ull << 31) && r.count > lseg) {
             g.C = (int)((r.count + lseg - 1) / lseg);
             g.lseg = lseg;
