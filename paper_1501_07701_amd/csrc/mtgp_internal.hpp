@@ -90,10 +90,11 @@ struct BatchItem {
 static_assert(sizeof(BatchItem) == 80, "BatchItem layout");
 
 // A BatchItem with MODE_GROUP: segments first .. first + n - 1 of a split
-// request (a whole request: lseg = count, prefix = 0).  Segment k covers outputs [start, end) of the request with
-// start = prefix (k = 0) or k * lseg and end = min(count, (k+1) * lseg); its
-// start state is states + k * N words, and its end state must equal segment
-// k+1's start state, or goes to state_out when it ends the request.
+// request (a whole request: lseg = count, prefix = 0).  Segment k covers
+// outputs [start, end) of the request with start = prefix (k = 0) or k * lseg
+// and end = min(count, (k+1) * lseg); its start state is states + k * N words,
+// and its end state must equal segment k+1's start state, or goes to state_out
+// when it ends the request.
 struct GroupItem {
     uint32_t stream;
     uint32_t mode;

@@ -1230,7 +1230,6 @@ __device__ __forceinline__ jv4 plane_read(uint32_t col, uint32_t bits, int s, in
 template <int T, int WPP>
 __device__ __forceinline__ void jump_block(const JumpBlock &jb, uint32_t *__restrict__ lds,
                                            uint32_t wave, uint32_t lane) {
-    constexpr int P = T * (T + 1) / 2;
     constexpr uint32_t PARTS = 4 / WPP;
     constexpr uint32_t CHUNK = T * JUMP_TILE;             // coefficients per chunk
     constexpr uint32_t STAGE = 2 * T * JUMP_TILE;         // words a chunk reads
