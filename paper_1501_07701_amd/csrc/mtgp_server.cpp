@@ -150,8 +150,9 @@ class HipBackend final : public SchedBackend {
         // command each, which refuses a destination that is too short
         int rc = MTGP_OK;
         std::vector<CopyPiece> pieces;
+        Range last;
         for (const Copy &c : copies) {
-            if (fits_here(c.dst, c.bytes)) {
+            if (fits_here(c.dst, c.bytes, last)) {
                 const uint64_t src = (uint64_t)(uintptr_t)(d_pool + c.off),
                                dst = (uint64_t)(uintptr_t)c.dst;
                 for (uint64_t o = 0; o < c.bytes; o += COPY_PIECE)
@@ -188,18 +189,29 @@ class HipBackend final : public SchedBackend {
     }
 
    private:
-    // Whether [dst, dst + bytes) lies in one allocation of this GPU's memory.
-    bool fits_here(void *dst, uint64_t bytes) const {
-        hipPointerAttribute_t at{};
-        hipDeviceptr_t base = nullptr;
-        size_t size = 0;
-        if (hipPointerGetAttributes(&at, dst) != hipSuccess || at.type != hipMemoryTypeDevice ||
-            at.device != device || hipMemGetAddressRange(&base, &size, dst) != hipSuccess) {
-            (void)hipGetLastError();  // the queries'
-            return false;
+    // An allocation of this GPU's memory.
+    struct Range {
+        uint64_t base = 0, size = 0;
+    };
+
+    // Whether [dst, dst + bytes) lies in one allocation of this GPU's memory;
+    // `last` holds the one found last (results mostly go to one buffer, and
+    // the two queries take longer than a short result's share of the copy).
+    bool fits_here(void *dst, uint64_t bytes, Range &last) const {
+        const uint64_t at = (uint64_t)(uintptr_t)dst;
+        if (at - last.base >= last.size) {
+            hipPointerAttribute_t a{};
+            hipDeviceptr_t base = nullptr;
+            size_t size = 0;
+            if (hipPointerGetAttributes(&a, dst) != hipSuccess || a.type != hipMemoryTypeDevice ||
+                a.device != device || hipMemGetAddressRange(&base, &size, dst) != hipSuccess) {
+                (void)hipGetLastError();  // the queries'
+                return false;
+            }
+            last = Range{(uint64_t)(uintptr_t)base, size};
+            if (at - last.base >= last.size) return false;
         }
-        const uint64_t off = (uint64_t)((char *)dst - (char *)base);
-        return off <= size && bytes <= size - off;
+        return bytes <= last.size - (at - last.base);
     }
 
     std::mutex copy_mu_;
