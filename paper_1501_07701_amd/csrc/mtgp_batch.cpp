@@ -1084,16 +1084,18 @@ int run_batch(const std::shared_ptr<ParamSet> &ps, const void *d_params, uint32_
     hipError_t e;
     const bool stamps = g_stamps.load();
     int ov = 0;
+    bool groups = false;  // (known where ov is)
     if (allow_overlap && !w.no_alloc && !stamps) {
         hipStreamCaptureStatus cst = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(s, &cst) == hipSuccess && cst == hipStreamCaptureStatusNone)
-            ov = overlap_groups(*ps, t, any_groups(*ps, reqs, t, w.shared_chip));
+        if (hipStreamIsCapturing(s, &cst) == hipSuccess && cst == hipStreamCaptureStatusNone) {
+            groups = any_groups(*ps, reqs, t, w.shared_chip);
+            ov = overlap_groups(*ps, t, groups);
+        }
     }
     if (ov) {
         // only a batch with both split and whole requests overlaps; for the
         // others the plan is the same either way, and phase-timed calls keep
         // using the cached one
-        const bool groups = any_groups(*ps, reqs, t, w.shared_chip);
         const uint64_t T = effective_target(*ps, reqs, t, groups);
         bool any_split = false, any_whole = false;
         const bool sparse = !w.shared_chip && is_sparse(*ps, reqs, T, t);
